@@ -123,7 +123,11 @@ typedef struct {
                              population, MRT) on all-periodic grids at most 6
                              (default 5 when that launch fills a third of the
                              device, else 1), with faces 1; D1Q3Q2 as the 1D
-                             grids above.  lbm_launch_info reports the choice. */
+                             grids above.  lbm_launch_info reports the choice.
+                             With 0, lbm_step may run the steps of several
+                             launches of the plan in one kernel, or those of one
+                             launch in several, where that is faster (1D); a
+                             depth asked for is kept. */
     void *f_a, *f_b;      /* caller-owned device state buffers (ping-pong) */
     void *stream;         /* hipStream_t; NULL = default stream */
     int adjoint_storage;  /* element type of adjoint buffers: 0 = the state's,
@@ -169,8 +173,9 @@ int lbm_current(lbm_ctx *ctx, void **state, long *steps_done);
 int lbm_launch_info(lbm_ctx *ctx, int *steps_per_launch, int *segment_rows,
                     long *resident_blocks);
 
-/* The launches lbm_step(ctx, nsteps) issues from the context's current step
- * count, in order (each advances the steps of the scheme of Sec. 2 eq.
+/* The launches of lbm_step(ctx, nsteps) from the context's current step
+ * count, in order (with fuse_steps = 0 lbm_step may regroup them, see there; each
+ * advances the steps of the scheme of Sec. 2 eq.
  * 2-relaxation some number of times; the state after any plan is bitwise the
  * same): ks[i] = steps of launch i, for i < min(launches, cap); *n_launches =
  * the number of launches (may be NULL).  Launches inside captured chunks are

@@ -149,6 +149,9 @@ struct lbm_ctx {
     Phys P;
     Launch L;
     int fuse;  // steps per launch (at most)
+    // Default plans (lbm_params.fuse_steps = 0): lbm_step regroups the plan's steps
+    // into kernels of at most this many; 0 = one kernel per launch of the plan.
+    int merge;
     bool x2;   // 2D two-step launches take the LDS strip kernel (all-periodic grids)
     void *buf[2];
     int cur;
@@ -180,13 +183,12 @@ static const int kChunk = 32;
 // fill the chip and the one-step kernel is faster (measured at 1024^2 and on the
 // 128^2 .. 1024^2 instances of the batched manifest).
 static const int kFuseMinBlocks = 1024;
-// 1D: steps per launch by default and at most (tiles of 1024 nodes hold the K
-// levels in LDS).
+// 1D: steps per launch of the plan by default and at most (lbm_step regroups default
+// plans, lbm_ctx.merge).
 static const int kDefaultFuse1d = 16;
 static const int kMaxFuse1d = 16;
-// 1D domains with non-periodic ends that fit one tile (step1k_whole): steps per
-// launch by default and at most (nothing is lost at the tile's ends; the 1000-node
-// dam break of 400 steps runs in one launch).
+// 1D domains with non-periodic ends that fit one workgroup (step1k_whole): steps per
+// launch of the plan by default and at most (nothing is lost at the ends).
 static const int kFuse1dWhole = 1024;
 static const int kFuseSeg = 24;  // rows per workgroup segment of the LDS two-step launch
 // Rows per wavefront segment of the wave-strip launch when the device cannot be
@@ -217,6 +219,9 @@ static const int kMaxFuse2d = 8;
 // Measured at 4096^2 (GLUPS for K = 2 .. 6): FP64 36.6, 56.5, 69.3, 105.1, 102.9;
 // FP32 53.8, 81.9, 102.4, 124.3, 120.6 (one step per launch: 26.9 / 57.5).
 static const int kDefaultFuseRest2d = 5;
+
+// Steps of one kernel of lbm_step, at most.
+static int step_depth(const lbm_ctx *c) { return c->merge > 0 ? c->merge : c->fuse; }
 
 extern "C" void lbm_destroy(lbm_ctx *c)
 {
@@ -387,7 +392,10 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     c->cur = 0;
     c->steps = 0;
     c->st = (hipStream_t)p->stream;
-    c->chunk_len = 2 * c->fuse * ((kChunk + 2 * c->fuse - 1) / (2 * c->fuse));
+    c->merge = dim == 1 && p->fuse_steps == 0 ? line_steps(c->G, rest, c->f32) : 0;
+    // regrouped kernels run long enough to be launched one by one
+    c->chunk_len =
+        c->merge > 0 ? 0 : 2 * c->fuse * ((kChunk + 2 * c->fuse - 1) / (2 * c->fuse));
 
     hipError_t e;
     const int nmb = moments_blocks(c->G);
@@ -445,13 +453,13 @@ static hipError_t step_once(lbm_ctx *c, const void *src, void *dst, hipStream_t 
     return launch_step(c->dim, c->f32, src, dst, c->G, c->P, c->L, st);
 }
 
-// k steps (1 <= k <= c->fuse) in one launch: level n in src, level n+k in dst.
+// k steps (1 <= k <= step_depth(c)) in one launch: level n in src, level n+k in dst.
 static hipError_t step_k(lbm_ctx *c, int k, const void *src, void *dst, hipStream_t st)
 {
     if (k == 1) return step_once(c, src, dst, st);
     if (c->rest)
         return c->dim == 1
-                   ? launch_step_rest1k(c->f32, src, dst, c->G, c->M, k, st)
+                   ? launch_line_rest(c->f32, src, dst, c->G, c->M, k, st)
                    : launch_step_rest2k(c->f32, src, dst, c->G, c->M, k, c->rest_seg_k[k], st);
     if (c->dim == 2) {
         if (c->x2 && k == 2)
@@ -459,7 +467,7 @@ static hipError_t step_k(lbm_ctx *c, int k, const void *src, void *dst, hipStrea
         const int seg = c->xk_seg_k[k] > 0 ? c->xk_seg_k[k] : c->xk_seg > 0 ? c->xk_seg : kXkSeg;
         return launch_step2k(c->f32, src, dst, c->G, c->P, k, seg, st);
     }
-    return launch_step1k(c->f32, src, dst, c->G, c->P, k, st);
+    return launch_line(c->f32, src, dst, c->G, c->P, k, st);
 }
 
 static int check_ctx(lbm_ctx *c)
@@ -514,38 +522,39 @@ static int ensure_chunk(lbm_ctx *c, int from)
     return LBM_OK;
 }
 
-// Steps of the next launch when `todo` steps remain outside the captured chunks.
-// Launches of `fuse` steps, except on 2D grids a remainder of two or more steps
+// Steps of the next launch when `todo` steps remain outside the captured chunks, at
+// most F per launch.  Launches of F steps, except on 2D grids a remainder of two or more steps
 // is spread over the last launches so that their step counts differ by at most
 // one: a 2D K-step launch takes nearly the same time for every K from 3 to 8
 // (the state is read and written once), so 20 steps run as 7 + 7 + 6 rather
 // than 8 + 8 + 4 (4096^2 FP64: 2.18 vs 2.29 ms).  A remainder of one step takes
-// the one-step kernel, the cheapest launch.
-static int next_launch_steps(const lbm_ctx *c, long todo)
+// the one-step kernel, the cheapest launch.  even: spread whatever the remainder
+// (regrouped kernels).
+static int next_launch_steps(const lbm_ctx *c, long F, bool even, long todo)
 {
-    const long F = c->fuse;
     if (todo <= 1 || F <= 1) return (int)(todo < 1 ? todo : 1);
     const long r = todo % F;
-    if (c->dim != 2 || r <= 1) return (int)(todo < F ? todo : F);
+    if (!even && (c->dim != 2 || r <= 1)) return (int)(todo < F ? todo : F);
     const long launches = (todo + F - 1) / F;
     return (int)((todo + launches - 1) / launches);
 }
 
-// Whether the next chunk_len / fuse launches of a `todo`-step run are all of
-// `fuse` steps (then a captured chunk can run them); todo >= chunk_len.
-static bool chunk_is_full(const lbm_ctx *c, long todo)
+// Whether the next chunk_len / F launches of a `todo`-step run are all of F steps
+// (then a captured chunk can run them); todo >= chunk_len.
+static bool chunk_is_full(const lbm_ctx *c, long F, bool even, long todo)
 {
-    for (int i = 0; i < c->chunk_len / c->fuse; ++i, todo -= c->fuse)
-        if (next_launch_steps(c, todo) != c->fuse) return false;
+    for (int i = 0; i < c->chunk_len / F; ++i, todo -= F)
+        if (next_launch_steps(c, F, even, todo) != F) return false;
     return true;
 }
 
-// The launches of nsteps steps from the context's step count, in order: chunk()
-// for a captured chunk of chunk_len steps, launch(k) for one launch of k steps,
-// check(at) for a state check after step `at`.  Stops at the first non-zero return.
+// The launches of nsteps steps from the context's step count, in order, at most F
+// steps each (even: next_launch_steps): chunk() for a captured chunk of chunk_len steps
+// (0: no chunks), launch(k) for one launch of k steps, check(at) for a state check
+// after step `at`.  Stops at the first non-zero return.
 template <typename Chunk, typename Launch, typename Check>
-static int walk_plan(const lbm_ctx *c, long nsteps, Chunk &&chunk, Launch &&launch,
-                     Check &&check)
+static int walk_plan(const lbm_ctx *c, long F, bool even, long chunk_len, long nsteps,
+                     Chunk &&chunk, Launch &&launch, Check &&check)
 {
     long done = 0, steps = c->steps;
     int rc;
@@ -557,14 +566,14 @@ static int walk_plan(const lbm_ctx *c, long nsteps, Chunk &&chunk, Launch &&laun
         }
         // chunks of full launches through the captured graph, the rest launch by launch
         while (todo > 0) {
-            if (todo >= c->chunk_len && chunk_is_full(c, todo)) {
+            if (chunk_len > 0 && todo >= chunk_len && chunk_is_full(c, F, even, todo)) {
                 if ((rc = chunk())) return rc;
-                todo -= c->chunk_len;
-                done += c->chunk_len;
-                steps += c->chunk_len;
+                todo -= chunk_len;
+                done += chunk_len;
+                steps += chunk_len;
                 continue;
             }
-            const int k = next_launch_steps(c, todo);
+            const int k = next_launch_steps(c, F, even, todo);
             if ((rc = launch(k))) return rc;
             todo -= k;
             done += k;
@@ -582,7 +591,7 @@ extern "C" int lbm_step(lbm_ctx *c, long nsteps)
     if (rc) return rc;
     if (nsteps < 0) return fail(LBM_EINVAL, "nsteps must be >= 0");
     return walk_plan(
-        c, nsteps,
+        c, step_depth(c), c->merge > 0, c->chunk_len, nsteps,
         [&]() -> int {
             int r = ensure_chunk(c, c->cur);
             if (r) return r;
@@ -611,11 +620,7 @@ extern "C" int lbm_launch_plan(lbm_ctx *c, long nsteps, int *ks, int cap, long *
         ++n;
     };
     rc = walk_plan(
-        c, nsteps,
-        [&]() -> int {
-            for (int i = 0; i < c->chunk_len / c->fuse; ++i) put(c->fuse);
-            return LBM_OK;
-        },
+        c, c->fuse, false, 0, nsteps, [&]() -> int { return LBM_OK; },
         [&](int k) -> int {
             put(k);
             return LBM_OK;

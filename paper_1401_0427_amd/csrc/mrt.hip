@@ -21,125 +21,11 @@
 //   f_xy^eq = f_yx^eq = rho u v, f_yy^eq = rho v^2 + p.
 // Plane order: rest population first, then the a = 0 order.
 #include "internal.h"
+#include "rest_device.h"
 #include "xk_wave.h"
 #include "multistep.h"
 
 namespace lbm {
-
-__device__ __forceinline__ void feq_rest1d(double h, double q, const Mrt &M, double *e)
-{
-    const double ih = 1.0 / h;
-    const double u = q * ih;
-    const double theta = M.g * h - 0.5 * (u * u);
-    const double f0 = M.aK * theta;
-    const double hr = h - f0;
-    const double p = M.hg * (h * h);
-    const double Fq = (q * q) * ih + p;
-    e[0] = f0;
-    e[1] = 0.5 * hr + q * M.c;
-    e[2] = 0.5 * hr - q * M.c;
-    e[3] = 0.5 * q + Fq * M.c;
-    e[4] = 0.5 * q - Fq * M.c;
-}
-
-__device__ __forceinline__ void feq_rest2d(double h, double qx, double qy, const Mrt &M, double *e)
-{
-    const double ih = 1.0 / h;
-    const double u = qx * ih, v = qy * ih;
-    const double theta = M.g * h - 0.5 * (u * u + v * v);
-    const double f0 = M.aK * theta;
-    const double hr = h - f0;
-    const double p = M.hg * (h * h);
-    const double Fxx = (qx * qx) * ih + p, Fxy = (qx * qy) * ih, Fyy = (qy * qy) * ih + p;
-    const double hq = 0.25 * hr, xq = 0.25 * qx, yq = 0.25 * qy;
-    e[0] = f0;
-    e[1] = hq + qx * M.c; e[2] = hq + qy * M.c; e[3] = hq - qx * M.c; e[4] = hq - qy * M.c;
-    e[5] = xq + Fxx * M.c; e[6] = xq + Fxy * M.c; e[7] = xq - Fxx * M.c; e[8] = xq - Fxy * M.c;
-    e[9] = yq + Fxy * M.c; e[10] = yq + Fyy * M.c; e[11] = yq - Fxy * M.c; e[12] = yq - Fyy * M.c;
-}
-
-__device__ __forceinline__ void collide_mrt1d(double *f, const Mrt &M)
-{
-    const double lam = M.lam, il = M.il;
-    const double sp = f[1] + f[2];
-    const double rho = f[0] + sp;
-    double J = lam * (f[1] - f[2]);
-    double eps = (lam * lam) * (sp - 2.0 * f[0]);
-    const double q = f[3] + f[4];
-    double Jq = lam * (f[3] - f[4]);
-    const double u = q / rho;
-    const double p = M.hg * (rho * rho);
-    const double theta = M.g * rho - 0.5 * (u * u);
-    J += M.rate[0] * (q - J);
-    eps += M.rate[1] * ((lam * lam) * (rho - 3.0 * (M.aK * theta)) - eps);
-    Jq += M.rate[2] * ((q * u + p) - Jq);
-    const double f0 = (rho - eps * (il * il)) / 3.0;
-    const double S = rho - f0;
-    f[0] = f0;
-    f[1] = 0.5 * (S + J * il);
-    f[2] = 0.5 * (S - J * il);
-    f[3] = 0.5 * (q + Jq * il);
-    f[4] = 0.5 * (q - Jq * il);
-}
-
-// Moments of one momentum family (g_1..g_4): total, x- and y-moments, XX.
-__device__ __forceinline__ void fam_moments(const double *g, double lam, double &q, double &mx,
-                                            double &my, double &xx)
-{
-    const double a = g[0] + g[2], b = g[1] + g[3];
-    q = a + b;
-    mx = lam * (g[0] - g[2]);
-    my = lam * (g[1] - g[3]);
-    xx = a - b;
-}
-
-__device__ __forceinline__ void fam_invert(double *g, double il, double q, double mx, double my,
-                                           double xx)
-{
-    const double a = 0.5 * (q + xx), b = 0.5 * (q - xx);
-    g[0] = 0.5 * (a + mx * il);
-    g[2] = 0.5 * (a - mx * il);
-    g[1] = 0.5 * (b + my * il);
-    g[3] = 0.5 * (b - my * il);
-}
-
-__device__ __forceinline__ void collide_mrt2d(double *f, const Mrt &M)
-{
-    const double lam = M.lam, il = M.il;
-    const double *r = M.rate;
-    const double s13 = f[1] + f[3], s24 = f[2] + f[4];
-    const double rho = f[0] + (s13 + s24);
-    double Jx = lam * (f[1] - f[3]);
-    double Jy = lam * (f[2] - f[4]);
-    double eps = (s13 + s24) - 4.0 * f[0];
-    double XX = s13 - s24;
-    double qx, fxx, fxy, XXu, qy, fyx, fyy, XXv;
-    fam_moments(f + 5, lam, qx, fxx, fxy, XXu);
-    fam_moments(f + 9, lam, qy, fyx, fyy, XXv);
-    const double ir = 1.0 / rho;
-    const double u = qx * ir, v = qy * ir;
-    const double p = M.hg * (rho * rho);
-    Jx += r[0] * (qx - Jx);
-    Jy += r[1] * (qy - Jy);
-    eps += r[2] * (((1.0 - 2.5 * M.a) * rho + (1.25 * M.a) * (u * u + v * v) / M.g) - eps);
-    XX += r[3] * (0.0 - XX);
-    fxx += r[4] * ((qx * u + p) - fxx);
-    fxy += r[5] * (qx * v - fxy);
-    XXu += r[6] * (0.0 - XXu);
-    fyx += r[7] * (qy * u - fyx);
-    fyy += r[8] * ((qy * v + p) - fyy);
-    XXv += r[9] * (0.0 - XXv);
-    const double f0 = 0.2 * (rho - eps);
-    const double S = rho - f0;
-    const double a = 0.5 * (S + XX), b = 0.5 * (S - XX);
-    f[0] = f0;
-    f[1] = 0.5 * (a + Jx * il);
-    f[3] = 0.5 * (a - Jx * il);
-    f[2] = 0.5 * (b + Jy * il);
-    f[4] = 0.5 * (b - Jy * il);
-    fam_invert(f + 5, il, qx, fxx, fxy, XXu);
-    fam_invert(f + 9, il, qy, fyx, fyy, XXv);
-}
 
 // ---- pulls (rest plane 0 does not move) ---------------------------------------------
 // An inflow face takes the equilibrium of its prescribed state, evaluated here in
@@ -376,113 +262,6 @@ __global__ void __launch_bounds__(256) k_step_rest2d_k(const T *__restrict__ src
             }
         }
     }
-}
-
-// ---- D1Q3Q2, K steps per launch ------------------------------------------------------
-// A workgroup of kK1Threads threads holds a tile of consecutive nodes, one per thread,
-// and advances it K steps with one barrier per step: the four moving planes go
-// through LDS (double-buffered), the rest population stays in the thread.  The tile
-// starts K nodes before its output nodes (each step invalidates one more node at
-// each tile edge), or, for a domain with non-periodic ends that fits one tile
-// (step1k_whole), covers the whole domain, whose ends apply the face rules, for any
-// K.  Faces as in the one-step kernel: Neumann takes the node's own value of the
-// plane, a wall its own opposite plane (momentum negated), an inflow face the
-// equilibrium of its state; levels rounded to the storage type, so a launch equals K
-// single steps bit for bit.
-__device__ __forceinline__ double rest1k_face(const Geo &G, int pl, int face, const double *own,
-                                              const double *weq)
-{
-    switch (G.bc[face]) {
-    case BC_NEUMANN:
-        return own[pl];
-    case BC_WALL: {
-        const int opp = pl == 1 ? 2 : pl == 2 ? 1 : pl == 3 ? 4 : 3;
-        const double v = own[opp];
-        return pl >= 3 ? -v : v;
-    }
-    default:  // BC_INFLOW
-        return weq[face * 5 + pl];
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(kK1Threads)
-    k_step_rest1d_k(const T *__restrict__ src, T *__restrict__ dst, Geo G, Mrt M, int K,
-                    int nout, int whole)
-{
-    constexpr int NT = kK1Threads;
-    __shared__ T sh[2][4][NT];
-    const int t = threadIdx.x;
-    const int nx = G.nx;
-    const long ps = G.ps;
-    const int ob = (int)blockIdx.x * nout;
-    const int x0 = whole ? 0 : ob - K;
-    const bool per = G.bc[0] == BC_PERIODIC;  // the two 1D faces are periodic together
-    const int oe = min(ob + nout, nx);         // output nodes [ob, oe)
-    const int x = x0 + t;                      // this thread's node, unwrapped
-    const bool in = per || (x >= 0 && x < nx);
-    const int xw = per ? ((x % nx) + nx) % nx : x;
-    const int tl = t > 0 ? t - 1 : t;  // clamped neighbours (edge values are invalid anyway)
-    const int tr = t < NT - 1 ? t + 1 : t;
-    double weq[10];
-#pragma unroll
-    for (int face = 0; face < 2; ++face)
-        if (G.bc[face] == BC_INFLOW) feq_rest1d(G.win[face][0], G.win[face][1], M, weq + 5 * face);
-    double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (in) {
-#pragma unroll
-        for (int pl = 0; pl < 5; ++pl) v[pl] = ld(src + pl * ps + xw);
-    }
-#pragma unroll
-    for (int pl = 1; pl < 5; ++pl) sh[0][pl - 1][t] = (T)v[pl];
-    __syncthreads();
-    int b = 0;
-    for (int k = 0; k < K; ++k) {
-        double f[5];
-        f[0] = v[0];
-        // f+ and g+ (planes 1, 3) from x - 1, f- and g- (planes 2, 4) from x + 1
-        if (!per && x == 0) {
-            f[1] = rest1k_face(G, 1, 0, v, weq);
-            f[3] = rest1k_face(G, 3, 0, v, weq);
-        } else {
-            f[1] = (double)sh[b][0][tl];
-            f[3] = (double)sh[b][2][tl];
-        }
-        if (!per && x == nx - 1) {
-            f[2] = rest1k_face(G, 2, 1, v, weq);
-            f[4] = rest1k_face(G, 4, 1, v, weq);
-        } else {
-            f[2] = (double)sh[b][1][tr];
-            f[4] = (double)sh[b][3][tr];
-        }
-        collide_mrt1d(f, M);
-        b ^= 1;
-#pragma unroll
-        for (int pl = 0; pl < 5; ++pl) v[pl] = (double)(T)f[pl];
-#pragma unroll
-        for (int pl = 1; pl < 5; ++pl) sh[b][pl - 1][t] = (T)v[pl];
-        __syncthreads();
-    }
-    if (in && x >= ob && x < oe) {
-#pragma unroll
-        for (int pl = 0; pl < 5; ++pl) sth<2>(dst + pl * ps + xw, v[pl]);
-    }
-}
-
-hipError_t launch_step_rest1k(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
-                              int K, hipStream_t st)
-{
-    const int whole = step1k_whole(G) ? 1 : 0;
-    if (K < 1 || (!whole && 2 * K >= kK1Threads)) return hipErrorInvalidValue;
-    const int nout = whole ? G.nx : kK1Threads - 2 * K;
-    const int nb = whole ? 1 : (G.nx + nout - 1) / nout;
-    if (f32)
-        hipLaunchKernelGGL(k_step_rest1d_k<float>, dim3(nb), dim3(kK1Threads), 0, st,
-                           (const float *)src, (float *)dst, G, M, K, nout, whole);
-    else
-        hipLaunchKernelGGL(k_step_rest1d_k<double>, dim3(nb), dim3(kK1Threads), 0, st,
-                           (const double *)src, (double *)dst, G, M, K, nout, whole);
-    return hipGetLastError();
 }
 
 template <typename T, int K>

@@ -16,9 +16,14 @@ int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out);
 long rest2k_blocks(const Geo &G, int K, int seg);
 hipError_t launch_step_rest2k(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
                               int K, int seg, hipStream_t st);
-// D1Q3Q2, K steps per launch: tiles of kK1Threads nodes with 2 K halo nodes (K < 512),
-// or one whole-domain tile for any K (step1k_whole); bitwise equal to K single steps.
-hipError_t launch_step_rest1k(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
-                              int K, hipStream_t st);
+// 1D (D1Q2 per component; D1Q3Q2), K steps per launch with the nodes in registers
+// (csrc/line.hip), any faces; bitwise equal to K single steps.  K at most 96, or
+// anything on a domain for which step1k_whole holds.
+hipError_t launch_line(bool f32, const void *src, void *dst, const Geo &G, const Phys &P, int K,
+                       hipStream_t st);
+hipError_t launch_line_rest(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
+                            int K, hipStream_t st);
+// Steps per kernel launch that are fastest on the domain (0: the whole run in one).
+int line_steps(const Geo &G, bool rest, bool f32);
 
 } // namespace lbm
