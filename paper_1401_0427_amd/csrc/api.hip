@@ -152,6 +152,7 @@ struct lbm_ctx {
     // Default plans (lbm_params.fuse_steps = 0): lbm_step regroups the plan's steps
     // into kernels of at most this many; 0 = one kernel per launch of the plan.
     int merge;
+    int tile;  // shape of the regrouped 2D launches
     bool x2;   // 2D two-step launches take the LDS strip kernel (all-periodic grids)
     void *buf[2];
     int cur;
@@ -392,7 +393,14 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     c->cur = 0;
     c->steps = 0;
     c->st = (hipStream_t)p->stream;
-    c->merge = dim == 1 && p->fuse_steps == 0 ? line_steps(c->G, rest, c->f32) : 0;
+    c->merge = 0;
+    if (p->fuse_steps == 0 && dim == 1) c->merge = line_steps(c->G, rest, c->f32);
+    if (p->fuse_steps == 0 && dim == 2) {
+        int k = 0;
+        // (a two-step plan is the LDS strip kernel, not a wave-strip one)
+        c->tile = tile2d_plan(c->G, rest, c->f32, c->fuse > 2, &k);
+        if (c->tile >= 0) c->merge = k;
+    }
     // regrouped kernels run long enough to be launched one by one
     c->chunk_len =
         c->merge > 0 ? 0 : 2 * c->fuse * ((kChunk + 2 * c->fuse - 1) / (2 * c->fuse));
@@ -457,6 +465,9 @@ static hipError_t step_once(lbm_ctx *c, const void *src, void *dst, hipStream_t 
 static hipError_t step_k(lbm_ctx *c, int k, const void *src, void *dst, hipStream_t st)
 {
     if (k == 1) return step_once(c, src, dst, st);
+    if (c->dim == 2 && c->merge > 0)
+        return c->rest ? launch_tile2d_rest(c->f32, c->tile, src, dst, c->G, c->M, k, st)
+                       : launch_tile2d(c->f32, c->tile, src, dst, c->G, c->P, k, st);
     if (c->rest)
         return c->dim == 1
                    ? launch_line_rest(c->f32, src, dst, c->G, c->M, k, st)

@@ -26,4 +26,13 @@ hipError_t launch_line_rest(bool f32, const void *src, void *dst, const Geo &G, 
 // Steps per kernel launch that are fastest on the domain (0: the whole run in one).
 int line_steps(const Geo &G, bool rest, bool f32);
 
+// 2D grids, K steps per launch of register tiles (csrc/tile2d.hip), any faces; bitwise
+// equal to K single steps.  tile2d_plan: the tile shape and the steps per launch for a
+// grid, or -1 where the wave-strip launches (strips: they fill the device) are faster.
+int tile2d_plan(const Geo &G, bool rest, bool f32, bool strips, int *K);
+hipError_t launch_tile2d(bool f32, int shape, const void *src, void *dst, const Geo &G,
+                         const Phys &P, int K, hipStream_t st);
+hipError_t launch_tile2d_rest(bool f32, int shape, const void *src, void *dst, const Geo &G,
+                              const Mrt &M, int K, hipStream_t st);
+
 } // namespace lbm
