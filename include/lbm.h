@@ -210,7 +210,8 @@ int lbm_moments(lbm_ctx *ctx, const void *state, double *h, double *qx, double *
  *     upstream node x - e_j (across a periodic face: wrapped), across a Neumann
  *     face the node's own plane j, across a wall its own opposite plane with the
  *     momentum normal to the face negated, across an inflow face nowhere;
- *   dLds_partials[b] += sum over block b of lam_np1 . (f^eq(W(v)) - v).
+ *   dLds_partials[b] += sum over the b-th group of nodes (1D: 256 in a row, 2D:
+ *     four columns of one row) of lam_np1 . (f^eq(W(v)) - v).
  * f_n: a caller buffer in the state layout and storage type; lam_np1, lam_n:
  * caller buffers in the state layout whose elements are of the context's
  * adjoint storage (lbm_params.adjoint_storage; lam_n must not alias the
@@ -225,24 +226,25 @@ long lbm_adjoint_partials(lbm_ctx *ctx);
 /* Backward sweep over one checkpoint segment in one call (the contexts of
  * lbm_adjoint_step),
  * for checkpointed gradients: from the state ck at level n0 (a caller buffer
- * in the state layout), recompute levels n0 + 1 .. n0 + nsteps - 1 by single
- * steps into work (nsteps - 1 consecutive state buffers of lbm_layout bytes
+ * in the state layout), recompute levels n0 + 1 .. n0 + nsteps - 1 into work
+ * (lbm_step_levels; nsteps - 1 consecutive state buffers of lbm_layout bytes
  * each; may be NULL when nsteps == 1), then apply nsteps adjoint steps
  * (lbm_adjoint_step) from lam^{n0 + nsteps}, held in lam_a, down to lam^{n0},
  * alternating between lam_a and lam_b (adjoint storage, not aliasing ck or
- * work).  *lam_out receives 0 when lam^{n0} ends in lam_a (nsteps even), 1 when
- * in lam_b.  Only enqueues kernels on the context's stream.  LBM_EINVAL for
- * nsteps < 1, null buffers or the contexts lbm_adjoint_step rejects. */
+ * work; several steps per launch on all-periodic 2D grids, bitwise the same).
+ * *lam_out receives 0 when lam^{n0} ends in lam_a (nsteps even), 1 when in lam_b.
+ * Only enqueues kernels on the context's stream.  LBM_EINVAL for nsteps < 1, null
+ * buffers or the contexts lbm_adjoint_step rejects. */
 int lbm_adjoint_segment(lbm_ctx *ctx, const void *ck, int nsteps, void *work, void *lam_a,
                         void *lam_b, double *dLds_partials, int *lam_out);
 
 /* Every level of a run kept, for gradients without recomputation when they fit
- * in device memory: nsteps single steps (lbm_step_buffers; the scheme of Sec. 2
- * eq. 2-relaxation) from the state `from`, writing level i into slot i - 1 of
- * levels (nsteps consecutive state buffers of lbm_layout bytes each), i = 1 ..
- * nsteps.  Does not touch the context's own buffers or step count.  Only
- * enqueues kernels.  LBM_EINVAL for nsteps < 0, null buffers, or `from`
- * overlapping levels. */
+ * in device memory: nsteps steps (bitwise those of lbm_step_buffers, several per
+ * launch where that is faster; the scheme of Sec. 2 eq. 2-relaxation) from the
+ * state `from`, writing level i into slot i - 1 of levels (nsteps consecutive
+ * state buffers of lbm_layout bytes each), i = 1 .. nsteps.  Does not touch the
+ * context's own buffers or step count.  Only enqueues kernels.  LBM_EINVAL for
+ * nsteps < 0, null buffers, or `from` overlapping levels. */
 int lbm_step_levels(lbm_ctx *ctx, const void *from, int nsteps, void *levels);
 
 /* Backward sweep over stored levels (the transposed steps of lbm_adjoint_step,

@@ -4,14 +4,14 @@
 initial height field h0 and the relaxation rate s.  The forward keeps a copy of
 the state every K steps (by default K is about sqrt(T)) and the backward, for
 each K-step segment in reverse, recomputes its states from the checkpoint (one
-extra forward step per adjoint step) and applies the hand-written adjoint kernel
-step by step -- one library call per segment (``lbm_adjoint_segment``).  With K =
-1 the forward keeps every level instead (single steps written level by level,
+extra forward step per adjoint step) and applies the hand-written adjoint kernels
+-- one library call per segment (``lbm_adjoint_segment``).  With K =
+1 the forward keeps every level instead (every step written to its slot,
 ``lbm_step_levels``) and the backward applies the adjoint over them in one
 library call (``lbm_adjoint_levels``), with no recomputation: the faster form
 whenever the T + 1 states fit in device memory (``every_level_fits``; 1024^2 FP32
 x 500 steps: 24 GB of an MI355X's 288).  Either way dL/ds
-accumulates in FP64 per workgroup, and finally dL/dh0 = J(W0)^T lam^0.  Every
+accumulates in FP64 per group of nodes, and finally dL/dh0 = J(W0)^T lam^0.  Every
 level is bitwise the same in both forms (multi-step launches equal single steps),
 so are the gradients.
 

@@ -13,7 +13,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
 SOURCES = ["api.hip", "fwd.hip", "adjoint.hip", "batch.hip", "mrt.hip", "entropy.hip", "tblock.hip",
-           "pbatch.hip", "line.hip", "tile2d.hip"]
+           "pbatch.hip", "line.hip", "tile2d.hip",
+           "adj_tile.hip"]
 ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 
 

@@ -15,41 +15,24 @@
 // where for each component family L0 = sum_j lam_j, L{x,y} = sum_j e_j lam_j
 // (Lxx: x-moment of the gx family, Lyx: y-moment of gx, Lxy: x-moment of gy).
 //
-// Each workgroup adds its share of dL/ds to its own FP64 slot (no atomics), so
-// the gradient is deterministic.  The adjoint may be stored in another type than
+// Each group of four columns of a row (1D: each workgroup) adds its share of dL/ds to
+// its own FP64 slot (no atomics), so the gradient is deterministic.  The adjoint may be stored in another type than
 // the state (TA = double for a float state keeps lambda in double; the
 // arithmetic is double throughout).
+#include "adj_device.h"
 #include "internal.h"
+#include "multistep.h"
 
 namespace lbm {
-
-__device__ __forceinline__ void adj_mu(const double *l, double h, double qx, double qy,
-                                       const Phys &P, double &mh, double &mx, double &my)
-{
-    const double ih = 1.0 / h;
-    const double u = qx * ih, v = qy * ih, gh = P.g * h;
-    const double L0h = (l[0] + l[2]) + (l[1] + l[3]);
-    const double Lxh = l[0] - l[2], Lyh = l[1] - l[3];
-    const double L0x = (l[4] + l[6]) + (l[5] + l[7]);
-    const double Lxx = l[4] - l[6], Lyx = l[5] - l[7];
-    const double L0y = (l[8] + l[10]) + (l[9] + l[11]);
-    const double Lxy = l[8] - l[10], Lyy = l[9] - l[11];
-    const double cross = Lyx + Lxy;
-    mh = 0.25 * L0h + P.c * (Lxx * (gh - u * u) - cross * (u * v) + Lyy * (gh - v * v));
-    mx = P.c * Lxh + 0.25 * L0x + P.c * (2.0 * u * Lxx + v * cross);
-    my = P.c * Lyh + 0.25 * L0y + P.c * (2.0 * v * Lyy + u * cross);
-}
 
 template <typename T, typename TA>
 __global__ void __launch_bounds__(256) k_adj2d(const T *__restrict__ un,
                                                const TA *__restrict__ lam1, TA *__restrict__ lam0,
                                                double *__restrict__ partials, Geo G, Phys P,
-                                               int tiles_x, int ntiles)
+                                               int tiles_x)
 {
-    __shared__ double sh[256];
-    const int t = xcd_tile(blockIdx.x, ntiles, false);  // plain order measured faster
-    const int y = t / tiles_x;
-    const int x = (t - y * tiles_x) * 256 + threadIdx.x;
+    const int y = blockIdx.x / tiles_x;
+    const int x = (blockIdx.x - y * tiles_x) * 256 + threadIdx.x;
     const int nx = G.nx, ny = G.ny;
     const long ps = G.ps;
     double acc = 0.0;
@@ -70,29 +53,18 @@ __global__ void __launch_bounds__(256) k_adj2d(const T *__restrict__ un,
         }
 #pragma unroll
         for (int pl = 0; pl < 12; ++pl) l[pl] = ld(lam1 + pl * ps + row + x);
-        double h, qx, qy, e[12], mu[3];
-        moments2d(v, h, qx, qy);
-        feq2d<T>(h, qx, qy, P, e);
-        adj_mu(l, h, qx, qy, P, mu[0], mu[1], mu[2]);
-#pragma unroll
-        for (int pl = 0; pl < 12; ++pl) acc += l[pl] * (e[pl] - v[pl]);
-        const double oms = 1.0 - P.s;
+        acc = adj_node2d<T>(v, l, P);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             TA *b = lam0 + (4 * k) * ps;
-            sth<2>(b + row + xm, oms * l[4 * k + 0] + P.s * mu[k]);
-            sth<2>(b + ps + rm + x, oms * l[4 * k + 1] + P.s * mu[k]);
-            sth<2>(b + 2 * ps + row + xp, oms * l[4 * k + 2] + P.s * mu[k]);
-            sth<2>(b + 3 * ps + rp + x, oms * l[4 * k + 3] + P.s * mu[k]);
+            sth<2>(b + row + xm, l[4 * k + 0]);
+            sth<2>(b + ps + rm + x, l[4 * k + 1]);
+            sth<2>(b + 2 * ps + row + xp, l[4 * k + 2]);
+            sth<2>(b + 3 * ps + rp + x, l[4 * k + 3]);
         }
     }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partials[blockIdx.x] += sh[0];
+    acc = group_sum(acc);
+    if (x < nx && x % kAdjGroup == 0) partials[adj_slot(nx, x, y)] += acc;
 }
 
 // ---- faces other than periodic ------------------------------------------------
@@ -144,7 +116,6 @@ __global__ void __launch_bounds__(256) k_adj2d_bnd(const T *__restrict__ un,
                                                    double *__restrict__ side, int side_len, Geo G,
                                                    Phys P, int tiles_x)
 {
-    __shared__ double sh[256];
     const int y = blockIdx.x / tiles_x;
     const int x = (blockIdx.x - y * tiles_x) * 256 + threadIdx.x;
     double acc = 0.0;
@@ -154,18 +125,12 @@ __global__ void __launch_bounds__(256) k_adj2d_bnd(const T *__restrict__ un,
         pull2d_generic(un, G, P, x, y, v);
 #pragma unroll
         for (int pl = 0; pl < 12; ++pl) l[pl] = ld(lam1 + pl * G.ps + row + x);
-        double h, qx, qy, e[12], mu[3];
-        moments2d(v, h, qx, qy);
-        feq2d<T>(h, qx, qy, P, e);
-        adj_mu(l, h, qx, qy, P, mu[0], mu[1], mu[2]);
-#pragma unroll
-        for (int pl = 0; pl < 12; ++pl) acc += l[pl] * (e[pl] - v[pl]);
-        const double oms = 1.0 - P.s;
+        acc = adj_node2d<T>(v, l, P);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                adj_push2d(lam0, side, side_len, G, k, j, x, y, oms * l[4 * k + j] + P.s * mu[k]);
+                adj_push2d(lam0, side, side_len, G, k, j, x, y, l[4 * k + j]);
         // slots whose +e_j side is a Neumann or inflow face receive nothing
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -179,13 +144,8 @@ __global__ void __launch_bounds__(256) k_adj2d_bnd(const T *__restrict__ un,
             }
         }
     }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partials[blockIdx.x] += sh[0];
+    acc = group_sum(acc);
+    if (x < G.nx && x % kAdjGroup == 0) partials[adj_slot(G.nx, x, y)] += acc;
 }
 
 // 1D: planes f+ (0), f- (1), g+ (2), g- (3); face 0 = x-, face 1 = x+.  With
@@ -196,7 +156,7 @@ __global__ void __launch_bounds__(256) k_adj2d_bnd(const T *__restrict__ un,
 __device__ __forceinline__ void adj_mu1d(const double *l, double h, double q, const Phys &P,
                                          double &mh, double &mq)
 {
-    const double u = q * (1.0 / h);
+    const double u = q * lbm_rcp(h);
     const double L1g = l[2] - l[3];
     mh = 0.5 * (l[0] + l[1]) + P.c * (P.g * h - u * u) * L1g;
     mq = P.c * (l[0] - l[1]) + 0.5 * (l[2] + l[3]) + 2.0 * u * P.c * L1g;
@@ -340,10 +300,36 @@ __global__ void __launch_bounds__(256) k_adj_grad_w0(const T *__restrict__ lam0,
     if (gqy) gqy[i] = my;
 }
 
+// Each workgroup sums one run of the input (fixed order); a second launch sums
+// the workgroups' results.  One workgroup over the 262 144 groups of a 1024^2 grid took
+// longer than several adjoint steps.
+__global__ void __launch_bounds__(256) k_sum_long(const double *__restrict__ in, long n,
+                                                  double *__restrict__ out)
+{
+    __shared__ double sh[256];
+    const long per = (n + gridDim.x - 1) / gridDim.x, b = (long)blockIdx.x * per;
+    const long e = b + per < n ? b + per : n;
+    double acc = 0.0;
+    for (long i = b + threadIdx.x; i < e; i += 256) acc += in[i];
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = sh[0];
+}
+
+hipError_t launch_sum_long(const double *in, long n, double *scratch, double *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_sum_long, dim3(kLongSum), dim3(256), 0, st, in, n, scratch);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_sum(scratch, kLongSum, 1, 1, out, st);
+}
+
 long adjoint_blocks(const Geo &G)
 {
-    const int tiles_x = (G.nx + 255) / 256;
-    return (long)tiles_x * G.ny;
+    return G.ny == 1 ? (G.nx + 255) / 256 : adj_slots_row(G.nx) * G.ny;  // 1D : 2D
 }
 
 static bool geo_periodic(const Geo &G)
@@ -362,8 +348,7 @@ static void adj_launch(int dim, const void *un, const void *lam1, void *lam0, do
                            (const TA *)lam1, (TA *)lam0, partials, side, side_len, G, P);
     else if (geo_periodic(G))
         hipLaunchKernelGGL((k_adj2d<T, TA>), dim3(tiles_x * G.ny), dim3(256), 0, st,
-                           (const T *)un, (const TA *)lam1, (TA *)lam0, partials, G, P, tiles_x,
-                           tiles_x * G.ny);
+                           (const T *)un, (const TA *)lam1, (TA *)lam0, partials, G, P, tiles_x);
     else
         hipLaunchKernelGGL((k_adj2d_bnd<T, TA>), dim3(tiles_x * G.ny), dim3(256), 0, st,
                            (const T *)un, (const TA *)lam1, (TA *)lam0, partials, side, side_len,

@@ -162,7 +162,7 @@ struct lbm_ctx {
     unsigned long long *d_speed;
     int *d_flag;
     double *d_partials;  // moments partials (3 per block)
-    double *d_totals;    // 3 doubles
+    double *d_totals;    // 4 doubles, then kLongSum of scratch
     double *d_adj_side;  // adjoint: own contributions of Neumann face nodes (if any)
     // captured step chunks, one per starting buffer
     hipStream_t cap;
@@ -410,7 +410,7 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     if ((e = hipMalloc(&c->d_speed, sizeof(unsigned long long))) != hipSuccess ||
         (e = hipMalloc(&c->d_flag, 2 * sizeof(int))) != hipSuccess ||
         (e = hipMalloc(&c->d_partials, sizeof(double) * 3 * (size_t)nmb)) != hipSuccess ||
-        (e = hipMalloc(&c->d_totals, sizeof(double) * 4)) != hipSuccess) {
+        (e = hipMalloc(&c->d_totals, sizeof(double) * (4 + kLongSum))) != hipSuccess) {
         lbm_destroy(c);
         return fail(LBM_EDEVICE, "hipMalloc of scratch failed: %s", hipGetErrorString(e));
     }
@@ -768,22 +768,77 @@ extern "C" int lbm_adjoint_step(lbm_ctx *c, const void *f_n, const void *lam_np1
     return LBM_OK;
 }
 
+// Steps of an adjoint sweep on an all-periodic 2D grid run several per launch: up to
+// adjoint_levels_steps (an odd number) over stored levels on small grids, two from every
+// second level on larger ones.  A sweep must end in the same one of its two buffers as
+// with one launch per step: odd launches keep that by themselves, pairs in even numbers.
+static bool multi_adjoint(const lbm_ctx *c)
+{
+    return c->dim == 2 && c->G.bc[0] == BC_PERIODIC && c->G.bc[2] == BC_PERIODIC;
+}
+// Of nsteps steps, the first this many (levels n0 ..) run in pairs.
+static int paired_steps(const lbm_ctx *c, int nsteps)
+{
+    const bool pairs = multi_adjoint(c) && adjoint_levels_steps(c->G) == 0 &&
+                       adjoint_pairs(c->G, c->f32, c->a32);
+    return pairs ? nsteps / 4 * 4 : 0;
+}
+
 // nsteps adjoint steps from lam^{n0 + nsteps} in lam_a down to lam^{n0}, level
-// n0 + i of the forward state at level(i); *lam_out = 0 when lam^{n0} ends in
-// lam_a, 1 when in lam_b.
+// n0 + i of the forward state at level(i) (consecutive buffers from i = 1 on); *lam_out = 0 when lam^{n0} ends in lam_a, 1 when
+// in lam_b.
 template <typename Level>
 static int adjoint_sweep(lbm_ctx *c, Level &&level, int nsteps, void *lam_a, void *lam_b,
                          double *dLds_partials, int *lam_out)
 {
+    const int paired = paired_steps(c, nsteps);
+    const int most = multi_adjoint(c) ? adjoint_levels_steps(c->G) : 0;
+    const long stride = (long)(c->bytes / (c->f32 ? 4 : 8));
     void *hi = lam_a, *lo = lam_b;
-    for (int i = nsteps - 1; i >= 0; --i) {
-        HIP_TRY(launch_adjoint(c->dim, c->f32, c->a32, level(i), hi, lo, dLds_partials,
-                               c->d_adj_side, c->G, c->P, c->st));
+    for (int i = nsteps; i > 0;) {
+        if (i <= paired) {
+            i -= 2;
+            HIP_TRY(launch_adjoint_pair(c->f32, c->a32, level(i), hi, lo, dLds_partials, c->G,
+                                        c->P, c->st));
+        } else if (most > 1 && i > 2) {
+            const int k = i < most ? (i - 1) | 1 : most;
+            i -= k;
+            HIP_TRY(launch_adjoint_levels(c->f32, c->a32, level(i), level(i + 1), stride, hi, lo,
+                                          dLds_partials, c->G, c->P, k, c->st));
+        } else {
+            --i;
+            HIP_TRY(launch_adjoint(c->dim, c->f32, c->a32, level(i), hi, lo, dLds_partials,
+                                   c->d_adj_side, c->G, c->P, c->st));
+        }
         void *t = hi;
         hi = lo;
         lo = t;
     }
     *lam_out = hi == lam_a ? 0 : 1;
+    return LBM_OK;
+}
+
+// Every level of nsteps steps from `from`, level i into slot i - 1 of levels.
+static int store_levels(lbm_ctx *c, const void *from, int nsteps, void *levels)
+{
+    const int tile = c->dim == 2 && !c->rest ? tile2d_levels_steps(c->G) : 0;
+    const int strip = !c->rest && multi_adjoint(c) ? levels_strip_steps(c->G, c->f32) : 0;
+    const int most = tile ? tile : strip;
+    const long stride = (long)(c->bytes / (c->f32 ? 4 : 8));
+    const void *prev = from;
+    for (int i = 0; i < nsteps;) {
+        void *dst = (char *)levels + (size_t)i * c->bytes;
+        const int left = nsteps - i, launches = most > 1 ? (left + most - 1) / most : left;
+        const int k = (left + launches - 1) / launches;
+        if (k > 1 && tile)
+            HIP_TRY(launch_tile2d_levels(c->f32, prev, dst, stride, c->G, c->P, k, c->st));
+        else if (k > 1)
+            HIP_TRY(launch_levels_strip(c->f32, prev, dst, stride, c->G, c->P, k, c->st));
+        else
+            HIP_TRY(step_once(c, prev, dst, c->st));
+        i += k;
+        prev = (char *)levels + (size_t)(i - 1) * c->bytes;
+    }
     return LBM_OK;
 }
 
@@ -801,8 +856,7 @@ extern "C" int lbm_adjoint_segment(lbm_ctx *c, const void *ck, int nsteps, void 
     auto level = [&](int i) -> const void * {
         return i == 0 ? ck : (const void *)((char *)work + (size_t)(i - 1) * c->bytes);
     };
-    for (int i = 1; i < nsteps; ++i)
-        HIP_TRY(step_once(c, level(i - 1), (void *)level(i), c->st));
+    if ((rc = store_levels(c, ck, nsteps - 1, work))) return rc;
     return adjoint_sweep(c, level, nsteps, lam_a, lam_b, dLds_partials, lam_out);
 }
 
@@ -822,13 +876,7 @@ extern "C" int lbm_step_levels(lbm_ctx *c, const void *from, int nsteps, void *l
     if (!from || !levels) return fail(LBM_EINVAL, "null buffer");
     if (overlaps(from, c->bytes, levels, (size_t)nsteps * c->bytes))
         return fail(LBM_EINVAL, "from must not overlap levels");
-    const void *prev = from;
-    for (int i = 0; i < nsteps; ++i) {
-        void *dst = (char *)levels + (size_t)i * c->bytes;
-        HIP_TRY(step_once(c, prev, dst, c->st));
-        prev = dst;
-    }
-    return LBM_OK;
+    return store_levels(c, from, nsteps, levels);
 }
 
 extern "C" int lbm_adjoint_levels(lbm_ctx *c, const void *levels, int nsteps, void *lam_a,
@@ -874,7 +922,10 @@ extern "C" int lbm_sum(lbm_ctx *c, const double *partials, long n, double *out_h
     int rc = check_ctx(c);
     if (rc) return rc;
     if (!partials || !out_host || n < 0) return fail(LBM_EINVAL, "bad argument");
-    HIP_TRY(launch_sum(partials, n, 1, 1, c->d_totals + 3, c->st));
+    if (n > 16 * kLongSum)
+        HIP_TRY(launch_sum_long(partials, n, c->d_totals + 4, c->d_totals + 3, c->st));
+    else
+        HIP_TRY(launch_sum(partials, n, 1, 1, c->d_totals + 3, c->st));
     HIP_TRY(hipMemcpyAsync(out_host, c->d_totals + 3, sizeof(double), hipMemcpyDeviceToHost,
                            c->st));
     HIP_TRY(hipStreamSynchronize(c->st));

@@ -35,4 +35,35 @@ hipError_t launch_tile2d(bool f32, int shape, const void *src, void *dst, const 
 hipError_t launch_tile2d_rest(bool f32, int shape, const void *src, void *dst, const Geo &G,
                               const Mrt &M, int K, hipStream_t st);
 
+// Two adjoint steps in one launch on an all-periodic 2D grid (csrc/adj_tile.hip): from
+// u^n and lambda^{n+2} to lambda^n and the dL/ds partials of both; bitwise equal to
+// the two one-step launches.
+bool adjoint_pairs(const Geo &G, bool f32, bool a32);  // whether the grid can run them
+hipError_t launch_adjoint_pair(bool f32, bool a32, const void *un, const void *lam2, void *lam0,
+                               double *partials, const Geo &G, const Phys &P, hipStream_t st);
+// Every level of K steps in one launch on larger all-periodic grids (csrc/adj_tile.hip):
+// level k + 1 at dst + k * stride elements, K up to kLevelStripMost.  levels_strip_steps:
+// the K of a grid, 0 where single steps have to do.
+constexpr int kLevelStripMost = 4;
+int levels_strip_steps(const Geo &G, bool f32);
+hipError_t launch_levels_strip(bool f32, const void *src, void *dst, long stride, const Geo &G,
+                               const Phys &P, int K, hipStream_t st);
+// Small 2D grids: K steps in one launch that stores every level (level k + 1 at dst + k *
+// stride elements; any faces), and K adjoint steps over stored levels (all-periodic;
+// level 0 at first, level j > 0 at next + (j - 1) * stride).  *_steps: K of the grid, 0
+// where single steps (two-step launches) are faster.
+int tile2d_levels_steps(const Geo &G);
+hipError_t launch_tile2d_levels(bool f32, const void *src, void *dst, long stride, const Geo &G,
+                                const Phys &P, int K, hipStream_t st);
+int adjoint_levels_steps(const Geo &G);
+hipError_t launch_adjoint_levels(bool f32, bool a32, const void *first, const void *next,
+                                 long stride, const void *lamK, void *lam0, double *partials,
+                                 const Geo &G, const Phys &P, int K, hipStream_t st);
+
+// Deterministic sum of n doubles into *out, n large: two launches, through kLongSum
+// doubles of scratch (csrc/adjoint.hip).
+constexpr int kLongSum = 256;
+hipError_t launch_sum_long(const double *in, long n, double *scratch, double *out,
+                           hipStream_t st);
+
 } // namespace lbm

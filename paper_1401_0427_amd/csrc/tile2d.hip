@@ -100,9 +100,12 @@ __device__ __forceinline__ void tile_pull(const TileFace &F, int face, const T *
     }
 }
 
-template <typename T, typename PH, bool BND, int TX, int TY, int R>
+// LEVELS: every level is stored, level k + 1 of the launch at dst + k * stride (else only
+// the last, at dst).
+template <typename T, typename PH, bool BND, bool LEVELS, int TX, int TY, int R>
 __global__ void __launch_bounds__(TX * TY)
-    k_tile2d(const T *__restrict__ src, T *__restrict__ dst, Geo G, PH P, int K, int ntx)
+    k_tile2d(const T *__restrict__ src, T *__restrict__ dst, long stride, Geo G, PH P, int K,
+             int ntx)
 {
     constexpr int NR = kTileRest<PH> ? 1 : 0;
     constexpr int NT = TX * TY;
@@ -133,6 +136,19 @@ __global__ void __launch_bounds__(TX * TY)
         }
     }
 
+    const bool ox = tx >= K && tx < TX - K && x < nx;
+    auto store = [&](T *out) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int y = y0 + r, i = ty * R + r;
+            if (ox && i >= K && i < TY * R - K && y < ny) {
+                T *d = out + (long)y * nx + x;
+                if constexpr (kTileRest<PH>) d[0] = r0[r];
+#pragma unroll
+                for (int pl = 0; pl < 12; ++pl) d[(NR + pl) * ps] = f[r][pl];
+            }
+        }
+    };
     auto steps = [&](auto xc, auto yc) __attribute__((always_inline)) {
         constexpr bool XF = decltype(xc)::value, YF = decltype(yc)::value;
         TileFace F[4]{};
@@ -211,6 +227,7 @@ __global__ void __launch_bounds__(TX * TY)
 #pragma unroll
                 for (int pl = 0; pl < 12; ++pl) f[r][pl] = (T)v[pl];
             }
+            if constexpr (LEVELS) store(dst + k * stride);
         }
     };
     if constexpr (BND) {
@@ -229,17 +246,7 @@ __global__ void __launch_bounds__(TX * TY)
         steps(std::false_type{}, std::false_type{});
     }
 
-    const bool ox = tx >= K && tx < TX - K && x < nx;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int y = y0 + r, i = ty * R + r;
-        if (ox && i >= K && i < TY * R - K && y < ny) {
-            T *d = dst + (long)y * nx + x;
-            if constexpr (kTileRest<PH>) d[0] = r0[r];
-#pragma unroll
-            for (int pl = 0; pl < 12; ++pl) d[(NR + pl) * ps] = f[r][pl];
-        }
-    }
+    if constexpr (!LEVELS) store(dst);
 }
 
 // ---- launchers -----------------------------------------------------------------------
@@ -324,9 +331,9 @@ int tile2d_plan(const Geo &G, bool rest, bool f32, bool strips, int *K)
     return shape;
 }
 
-template <typename T, typename PH, int TX, int TY, int R>
-static hipError_t tile_launch(const void *src, void *dst, const Geo &G, const PH &P, int K,
-                              hipStream_t st)
+template <typename T, typename PH, bool LEVELS, int TX, int TY, int R>
+static hipError_t tile_launch(const void *src, void *dst, long stride, const Geo &G, const PH &P,
+                              int K, hipStream_t st)
 {
     const int wo = TX - 2 * K, ho = TY * R - 2 * K;
     if (K < 1 || wo < 1 || ho < 1) return hipErrorInvalidValue;
@@ -334,11 +341,11 @@ static hipError_t tile_launch(const void *src, void *dst, const Geo &G, const PH
     if ((long)ntx * nty > 0x7fffffffL) return hipErrorInvalidValue;
     const bool bnd = G.bc[0] != BC_PERIODIC || G.bc[2] != BC_PERIODIC;
     if (bnd)
-        hipLaunchKernelGGL((k_tile2d<T, PH, true, TX, TY, R>), dim3(ntx * nty), dim3(TX * TY), 0,
-                           st, (const T *)src, (T *)dst, G, P, K, ntx);
+        hipLaunchKernelGGL((k_tile2d<T, PH, true, LEVELS, TX, TY, R>), dim3(ntx * nty),
+                           dim3(TX * TY), 0, st, (const T *)src, (T *)dst, stride, G, P, K, ntx);
     else
-        hipLaunchKernelGGL((k_tile2d<T, PH, false, TX, TY, R>), dim3(ntx * nty), dim3(TX * TY), 0,
-                           st, (const T *)src, (T *)dst, G, P, K, ntx);
+        hipLaunchKernelGGL((k_tile2d<T, PH, false, LEVELS, TX, TY, R>), dim3(ntx * nty),
+                           dim3(TX * TY), 0, st, (const T *)src, (T *)dst, stride, G, P, K, ntx);
     return hipGetLastError();
 }
 
@@ -347,13 +354,13 @@ static hipError_t tile_any(int shape, const void *src, void *dst, const Geo &G, 
                            int K, hipStream_t st)
 {
     switch (shape) {
-    case kTile16: return tile_launch<T, PH, 16, 16, 1>(src, dst, G, P, K, st);
-    case kTile32x16: return tile_launch<T, PH, 32, 16, 1>(src, dst, G, P, K, st);
-    case kTile32: return tile_launch<T, PH, 32, 16, 2>(src, dst, G, P, K, st);
-    case kTile64x32: return tile_launch<T, PH, 64, 8, 4>(src, dst, G, P, K, st);
+    case kTile16: return tile_launch<T, PH, false, 16, 16, 1>(src, dst, 0, G, P, K, st);
+    case kTile32x16: return tile_launch<T, PH, false, 32, 16, 1>(src, dst, 0, G, P, K, st);
+    case kTile32: return tile_launch<T, PH, false, 32, 16, 2>(src, dst, 0, G, P, K, st);
+    case kTile64x32: return tile_launch<T, PH, false, 64, 8, 4>(src, dst, 0, G, P, K, st);
     case kTile32Tall:
         if constexpr (sizeof(T) == 8)
-            return tile_launch<T, PH, 32, 8, 4>(src, dst, G, P, K, st);
+            return tile_launch<T, PH, false, 32, 8, 4>(src, dst, 0, G, P, K, st);
         break;
     default: break;
     }
@@ -371,6 +378,46 @@ hipError_t launch_tile2d_rest(bool f32, int shape, const void *src, void *dst, c
 {
     return f32 ? tile_any<float>(shape, src, dst, G, M, K, st)
                : tile_any<double>(shape, src, dst, G, M, K, st);
+}
+// Shapes and depths of launches that store every level, by nodes (us per level FP32 /
+// FP64 against single steps, at 96 x 64, 160^2, 256^2, 512^2, 724^2: 1.1 / 1.2 against
+// 3.0, 1.4 / 1.7 against 3.1, 2.3 / 2.9 against 3.3 / 4.1, 5.8 / 7.0 against 6.8 / 12,
+// 11.2 / 18.5 against 12.6 / 22.4).  Beyond the last line the strips that store every
+// level take over on all-periodic grids (724^2: 10.7 / 19.0, 1024^2 FP64 29.7 against
+// 35.4), single steps with faces (1024^2 FP32 20.6 against 21.4).
+static const struct {
+    long nodes;  // at most
+    int shape, K;
+} kLevelShapes[] = {
+    {12000, kTile16, 5}, {50000, kTile32x16, 5}, {120000, kTile32x16, 4}, {700000, kTile64x32, 4}};
+
+int tile2d_levels_steps(const Geo &G)
+{
+    for (const auto &s : kLevelShapes)
+        if ((long)G.nx * G.ny <= s.nodes) return s.K;
+    return 0;
+}
+
+template <typename T>
+static hipError_t levels_any(const void *src, void *dst, long stride, const Geo &G, const Phys &P,
+                             int K, hipStream_t st)
+{
+    for (const auto &s : kLevelShapes) {
+        if ((long)G.nx * G.ny > s.nodes) continue;
+        switch (s.shape) {
+        case kTile16: return tile_launch<T, Phys, true, 16, 16, 1>(src, dst, stride, G, P, K, st);
+        case kTile32x16:
+            return tile_launch<T, Phys, true, 32, 16, 1>(src, dst, stride, G, P, K, st);
+        default: return tile_launch<T, Phys, true, 64, 8, 4>(src, dst, stride, G, P, K, st);
+        }
+    }
+    return hipErrorInvalidValue;
+}
+hipError_t launch_tile2d_levels(bool f32, const void *src, void *dst, long stride, const Geo &G,
+                                const Phys &P, int K, hipStream_t st)
+{
+    return f32 ? levels_any<float>(src, dst, stride, G, P, K, st)
+               : levels_any<double>(src, dst, stride, G, P, K, st);
 }
 
 } // namespace lbm
