@@ -97,13 +97,13 @@ FACES_INFLOW = {0: (1.0, 0.2, 0.0), 3: (1.0, 0.0, -0.2)}
 def time_forward(torch, n, storage, steps, warmup, block, npt, pad, fuse=1, keep_h=False,
                  bc=("periodic",) * 4, inflow=None):
     """Forward steps of the headline workload; ``fuse`` = steps per launch asked
-    for (0 = the library's choice; lbm_launch_info reports what runs).  The timed
-    region issues the library's own plan for ``steps`` steps (lbm_launch_plan:
-    launches of K steps, a remainder of two or more spread evenly over the last
-    launches) one launch per lbm_step call, with a HIP event on the launch stream
-    after each, so the average duration of the launches of the dominant kernel
-    (the most frequent steps per launch of the plan) is measured directly.  With
-    ``keep_h`` the final height field is returned under "h"."""
+    for (0 = the library's choice; lbm_launch_info reports its plan).  The timed
+    region is one lbm_step call of ``steps`` steps, which regroups a default plan
+    into its fastest launches.  After it (and the final fields) the plan of
+    lbm_launch_plan is issued one launch per call with a HIP event after each, for
+    the average duration of the launches of the dominant kernel (the most frequent
+    steps per launch of the plan).  With ``keep_h`` the final height field is
+    returned under "h"."""
     from paper_1401_0427_amd import workloads as W
     from paper_1401_0427_amd.lbm import Solver
 
@@ -121,16 +121,20 @@ def time_forward(torch, n, storage, steps, warmup, block, npt, pad, fuse=1, keep
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(pieces) + 1)]
     t0 = time.perf_counter()
     ev[0].record(st)
+    S.step(steps)
+    ev[-1].record(st)
+    torch.cuda.synchronize()
+    wall = time.perf_counter() - t0
+    ms = ev[0].elapsed_time(ev[-1])
+    (h, _, _), tot = S.moments(totals=True)
+    ok = bool(torch.isfinite(h).all().item()) and tot[0] > 0
+    ev[0].record(st)
     for i, k in enumerate(pieces):
         S.step(k)
         ev[i + 1].record(st)
     torch.cuda.synchronize()
-    wall = time.perf_counter() - t0
-    ms = ev[0].elapsed_time(ev[-1])
     dur = [ev[i].elapsed_time(ev[i + 1]) for i in range(len(pieces))]
     full = [d for d, k in zip(dur, pieces) if k == Kd]
-    (h, _, _), tot = S.moments(totals=True)
-    ok = bool(torch.isfinite(h).all().item()) and tot[0] > 0
     nodes = n * n
     bpl = 12 * 2 * (8 if storage == "f64" else 4)  # algorithmic bytes per lattice update
     out_h = {"h": h.clone()} if keep_h else {}
@@ -141,9 +145,9 @@ def time_forward(torch, n, storage, steps, warmup, block, npt, pad, fuse=1, keep
                 launch_steps={str(k): pieces.count(k) for k in sorted(set(pieces), reverse=True)},
                 dominant_steps=Kd, periodic=all(b == "periodic" for b in bc),
                 segment_rows=info["segment_rows"], resident_blocks=info["resident_blocks"],
-                ms_per_launch=(sum(full) / len(full)) if full else ms / len(pieces),
+                ms_per_launch=sum(full) / len(full),
                 full_launches=len(full),
-                gbs=nodes * bpl * len(pieces) / (ms * 1e-3) / 1e9, bytes_per_lu=bpl,
+                gbs=nodes * bpl * len(pieces) / (sum(dur) * 1e-3) / 1e9, bytes_per_lu=bpl,
                 bytes_per_launch=nodes * bpl, wall_s=wall, finite=ok, mass=tot[0])
 
 

@@ -153,8 +153,8 @@ int lbm_init(const lbm_params *p, const double *h0, const double *qx0, const dou
 /* Advance nsteps fused pull-stream + collide steps (ping-pong between f_a and
  * f_b): the transport along the lattice velocities then the relaxation of Sec. 2
  * eq. 2-relaxation (Sec. 3 for the D2Q4 vectorial scheme), with the face rules of
- * the Sec. 3 boundary paragraph.  Launches as lbm_launch_plan lists them; the
- * state does not depend on the plan.  Stream-ordered; with check_every > 0 it
+ * the Sec. 3 boundary paragraph.  Launches as lbm_launch_plan lists them, default
+ * plans regrouped; the state does not depend on the plan.  Stream-ordered; with check_every > 0 it
  * synchronises at each check. */
 int lbm_step(lbm_ctx *ctx, long nsteps);
 

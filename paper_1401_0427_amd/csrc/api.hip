@@ -152,7 +152,7 @@ struct lbm_ctx {
     // Default plans (lbm_params.fuse_steps = 0): lbm_step regroups the plan's steps
     // into kernels of at most this many; 0 = one kernel per launch of the plan.
     int merge;
-    int tile;  // shape of the regrouped 2D launches
+    int tile;  // shape of the regrouped 2D launches; -1: wave strips
     bool x2;   // 2D two-step launches take the LDS strip kernel (all-periodic grids)
     void *buf[2];
     int cur;
@@ -379,9 +379,10 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     }
     // launches of fewer steps (the plan's shorter launches) take the segment
     // length chosen for their own depth: their kernels hold fewer registers, so
-    // more workgroups are resident than for the full-depth launch
+    // more workgroups are resident than for the full-depth launch (default plans:
+    // step2k_rows, below)
     for (int k = 0; k <= 16; ++k) c->xk_seg_k[k] = 0;
-    if (dim == 2 && c->xk_seg > 0)
+    if (dim == 2 && c->xk_seg > 0 && p->fuse_steps != 0)
         for (int k = 2; k <= c->fuse && k <= kMaxFuse2d; ++k) {
             if (k == 2 && c->x2) continue;
             const int sk = k == c->fuse ? c->xk_seg
@@ -394,12 +395,22 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     c->steps = 0;
     c->st = (hipStream_t)p->stream;
     c->merge = 0;
+    c->tile = -1;
     if (p->fuse_steps == 0 && dim == 1) c->merge = line_steps(c->G, rest, c->f32);
     if (p->fuse_steps == 0 && dim == 2) {
         int k = 0;
         // (a two-step plan is the LDS strip kernel, not a wave-strip one)
         c->tile = tile2d_plan(c->G, rest, c->f32, c->fuse > 2, &k);
-        if (c->tile >= 0) c->merge = k;
+        if (c->tile >= 0) {
+            c->merge = k;
+        } else if (!rest && c->xk_seg > 0) {
+            // wave-strip launches, with their own depth and segments
+            c->merge = c->x2 && !c->f32 ? kXkDeepF64 : c->fuse;
+            for (int k2 = 2; k2 <= c->merge; ++k2) {
+                const int sk = step2k_rows(c->G, c->f32, k2);
+                c->xk_seg_k[k2] = sk > 0 ? sk : c->xk_seg;
+            }
+        }
     }
     // regrouped kernels run long enough to be launched one by one
     c->chunk_len =
@@ -465,7 +476,7 @@ static hipError_t step_once(lbm_ctx *c, const void *src, void *dst, hipStream_t 
 static hipError_t step_k(lbm_ctx *c, int k, const void *src, void *dst, hipStream_t st)
 {
     if (k == 1) return step_once(c, src, dst, st);
-    if (c->dim == 2 && c->merge > 0)
+    if (c->tile >= 0)
         return c->rest ? launch_tile2d_rest(c->f32, c->tile, src, dst, c->G, c->M, k, st)
                        : launch_tile2d(c->f32, c->tile, src, dst, c->G, c->P, k, st);
     if (c->rest)

@@ -146,16 +146,18 @@ hipError_t launch_adjoint_grad_w0(int dim, bool f32, const void *lam0, const dou
                                   double *gqy, const Geo &G, const Phys &P, hipStream_t st);
 
 int step2x_blocks(const Geo &G, int seg);
-// 1D K-step launch: tiles of kK1Threads nodes with 2 K halo nodes (K < 512), or,
-// for a domain with non-periodic ends of at most kK1Threads nodes (step1k_whole),
-// one whole-domain tile and any K.
+// A 1D domain with non-periodic ends that fits one workgroup (kK1Threads nodes).
 bool step1k_whole(const Geo &G);
-hipError_t launch_step1k(bool f32, const void *src, void *dst, const Geo &G, const Phys &P,
-                         int K, hipStream_t st);
 hipError_t launch_step2x(bool f32, const void *src, void *dst, const Geo &G, const Phys &P,
                          int seg, hipStream_t st);
 int step2k_blocks(const Geo &G, bool f32, int K, int seg);
 int step2k_seg(const Geo &G, bool f32, int K, int min_seg, bool *full, long *slots_out);
+// Depth of the regrouped launches of default plans on all-periodic FP64 grids: 9 steps
+// leave the same 48 output columns of 64 as 8 (16 halo lanes) and take 730 us at 4096^2
+// where 8 take 708 (81 against 88 us a step); 10 leave 40.  FP32: 8 (9 takes the 256-lane
+// strips to two workgroups per compute unit: 62 against 56 us a step).
+constexpr int kXkDeepF64 = 9;
+int step2k_rows(const Geo &G, bool f32, int K);  // segment rows of those launches
 int step2k_max_k_bounded();  // steps per launch at most with non-periodic faces
 int step2k_default_k_bounded(bool f32);  // and by default
 

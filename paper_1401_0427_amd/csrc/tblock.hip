@@ -259,6 +259,7 @@ static int xk_wo_of(bool f32, int K, bool bnd = false, int sw = 1)
     case 5: return f32 ? xk_wo<float, 5>() : xk_wo<double, 5>();
     case 6: return f32 ? xk_wo<float, 6>() : xk_wo<double, 6>();
     case 7: return f32 ? xk_wo<float, 7>() : xk_wo<double, 7>();
+    case 9: return xk_wo<double, 9>();  // (FP64 only)
     default: return f32 ? xk_wo<float, 8>() : xk_wo<double, 8>();
     }
 }
@@ -347,6 +348,11 @@ static int xk_per_cu(bool f32, int K, bool bnd)
         LBM_XK_OCC(6)
         LBM_XK_OCC(7)
         LBM_XK_OCC(8)
+    case 9:
+        if (!bnd && !f32)
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &n, k_step2d_xk<double, 9, kXkDepth>, bs, 0);
+        break;
     default:
         break;
     }
@@ -397,6 +403,43 @@ int step2k_seg(const Geo &G, bool f32, int K, int min_seg, bool *full, long *slo
     return best;
 }
 
+// Rows per segment for the regrouped launches of default plans.  The launch time follows
+// the workgroups on the fullest compute unit, not their number: with one, two and three
+// of them an iteration takes 1, 1.65 and 2.35 times as long (2.2, 3.7 and 5.1 us; one
+// workgroup nearly saturates the FP64 units), and the start of a segment costs about 1.3
+// iterations per level (warm iterations run only the levels that have rows).  So segments
+// are as long as a whole number of workgroups per compute unit allows: 1448^2 FP32, 6
+// steps, 85 segments of 18 rows (two each) 10.7 us a step, 91 of 16 (three on some) 14.0;
+// 1024^2 FP64, 9 steps, 41 of 25 (one each) 9.4, 64 of 16 11.5.  0 when the device cannot
+// be queried.
+int step2k_rows(const Geo &G, bool f32, int K)
+{
+    static const double kIter[4] = {0.0, 1.0, 1.65, 2.35};
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    int per = xk_per_cu(f32, K, geo_bounded(G));
+    if (per <= 0 || ncu <= 0) return 0;
+    if (per > 3) per = 3;
+    const long ngroups = step2k_groups(G, f32, K);
+    int best = 0;
+    double best_cost = 0.0;
+    for (int nseg = 1; nseg <= G.ny; ++nseg) {
+        const int seg = (G.ny + nseg - 1) / nseg;
+        if (seg < 8 && nseg > 1) break;
+        if ((G.ny + seg - 1) / seg != nseg) continue;  // same seg as a smaller nseg
+        const long n = (ngroups * nseg + ncu - 1) / ncu;
+        const double cost =
+            ((double)(n / per) * kIter[per] + kIter[n % per]) * (seg + 1.3 * K);
+        if (best == 0 || cost < best_cost) {
+            best = seg;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_step2k(bool f32, const void *src, void *dst, const Geo &G, const Phys &P,
                          int K, int seg, hipStream_t st)
 {
@@ -428,6 +471,11 @@ hipError_t launch_step2k(bool f32, const void *src, void *dst, const Geo &G, con
         LBM_XK_CASE(6)
         LBM_XK_CASE(7)
         LBM_XK_CASE(8)
+    case 9:
+        if (bnd || f32) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_step2d_xk<double, 9, kXkDepth>), grid, block, 0, st,
+                           (const double *)src, (double *)dst, G, P, ns, seg);
+        break;
     default:
         return hipErrorInvalidValue;
     }
@@ -435,17 +483,6 @@ hipError_t launch_step2k(bool f32, const void *src, void *dst, const Geo &G, con
     return hipGetLastError();
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kK1Threads)
-    k_step1d_k(const T *__restrict__ src, T *__restrict__ dst, Geo G, Phys P, int K, int nout,
-               int whole)
-{
-    __shared__ T sh[2][4][kK1Threads];
-    const int ob = (int)blockIdx.x * nout;
-    k1_tile<T, kK1Threads>(src, dst, G, P, K, whole ? 0 : ob - K, ob, nout, sh);
-}
-
-// Batched form: workgroup b takes 1D tile b of a table spanning many 1D instances.
 template <typename T>
 __global__ void __launch_bounds__(kK1Threads)
     k_batch_1k(const InstDev *__restrict__ inst, const K1TileDev *__restrict__ tiles,
@@ -459,23 +496,6 @@ __global__ void __launch_bounds__(kK1Threads)
 }
 
 bool step1k_whole(const Geo &G) { return G.bc[0] != BC_PERIODIC && G.nx <= kK1Threads; }
-
-hipError_t launch_step1k(bool f32, const void *src, void *dst, const Geo &G, const Phys &P,
-                         int K, hipStream_t st)
-{
-    // a domain with non-periodic ends that fits one tile: one workgroup, any K
-    const int whole = step1k_whole(G) ? 1 : 0;
-    if (!whole && 2 * K >= kK1Threads) return hipErrorInvalidValue;
-    const int nout = whole ? G.nx : kK1Threads - 2 * K;
-    const int nb = whole ? 1 : (G.nx + nout - 1) / nout;
-    if (f32)
-        hipLaunchKernelGGL(k_step1d_k<float>, dim3(nb), dim3(kK1Threads), 0, st,
-                           (const float *)src, (float *)dst, G, P, K, nout, whole);
-    else
-        hipLaunchKernelGGL(k_step1d_k<double>, dim3(nb), dim3(kK1Threads), 0, st,
-                           (const double *)src, (double *)dst, G, P, K, nout, whole);
-    return hipGetLastError();
-}
 
 int step2x_blocks(const Geo &G, int seg)
 {

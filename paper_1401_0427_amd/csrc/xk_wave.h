@@ -424,11 +424,17 @@ struct XkLds {
 // the grid, also past the segment's end).  em: e2 planes of each intermediate
 // level one row below the row this iteration consumes (it is overwritten with
 // the newest row, the other array then holding the older one).  There is no
-// branch: levels without a valid row yet (the first 2 (K - 1) iterations) and
-// iterations past the end compute values that are never stored nor reach a
-// stored value, and their stores, like those of non-output lanes, carry an
+// branch: iterations past the end compute values that are never stored nor reach
+// a stored value, and their stores, like those of non-output lanes, carry an
 // offset the hardware drops -- so the compiler's memory waits see one straight
 // sequence and keep the D rows of loads in flight.
+// WARM (the first 2 (K - 1) iterations, which store nothing): level k + 1 has its
+// first row that anything needs at iteration 2 k, so iteration j skips the
+// collisions of the levels beyond (one uniform branch per level) -- half of the
+// work before a segment's first output.  Every pull, exchange and rounding stays,
+// so the loop's registers are those of the other iterations.  Measured, us a step
+// without and with: 4096^2 FP64 K = 8 94.7 / 92.2, FP32 66 / 64, 1792 x 1024 with
+// faces FP64 K = 7 (segments of 21 rows) 19.2 / 17.6.
 // Grids with non-periodic faces (BND): s1 / s3 hold the lane's own e1 / e3
 // planes of the last row, unshifted, and the exchange happens where they are
 // used (DPP), so a face lane can take its own values instead; ec is the other
@@ -440,8 +446,8 @@ struct XkLds {
 // receives the face value; on a Neumann y+ face the e2 slot of row ny - 1 (read
 // only by row ny, outside the grid) receives its own e4 planes, which row
 // ny - 1 pulls back.
-// X: the wavefront's LDS offsets for this row (XkLds).
-template <typename T, int K, bool BND, int SW = 1>
+// X: the wavefront's LDS offsets for this row (XkLds); j: the iteration.
+template <typename T, int K, bool BND, int SW, bool WARM>
 __device__ __forceinline__ void xk_row(const T *__restrict__ src, long ps, const Phys &P,
                                        int lane, const __amdgpu_buffer_rsrc_t *orsrc,
                                        unsigned ooff, const XkOff &onext, const T (&cur)[12],
@@ -449,7 +455,7 @@ __device__ __forceinline__ void xk_row(const T *__restrict__ src, long ps, const
                                        T (&s3)[K - 1][3], T (&pend)[12], unsigned &pend_off,
                                        T *__restrict__ lds, const Geo &G, const XkBnd &B, int i,
                                        int inext, int xm, int xw, int xp, bool bx0, bool bx1,
-                                       T (&ec)[K - 1][3], const XkLds &X)
+                                       T (&ec)[K - 1][3], const XkLds &X, int j)
 {
     constexpr int L = BND ? 0 : xk_lds_levels_sw<T, K, SW>();
     constexpr int LB = BND ? xkb_lds_levels<T, K>() : 0;
@@ -498,8 +504,10 @@ __device__ __forceinline__ void xk_row(const T *__restrict__ src, long ps, const
     // which counts stores and loads together, does not stall on this row's
     // stores.  The scheduling barrier keeps that order.
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!WARM) {
 #pragma unroll
-    for (int pl = 0; pl < 12; ++pl) xk_store(orsrc[pl], pend_off, pend[pl]);
+        for (int pl = 0; pl < 12; ++pl) xk_store(orsrc[pl], pend_off, pend[pl]);
+    }
     if constexpr (BND)
         xk_load_clamp(src, ps, G, B, inext, xm, xw, xp, nxt);
     else
@@ -666,7 +674,12 @@ __device__ __forceinline__ void xk_row(const T *__restrict__ src, long ps, const
                 }
                 if constexpr (SW > 1) __asm__ __volatile__("" ::: "memory");
             }
-            collide2d<T>(o, P);
+            if constexpr (WARM) {
+                // rounded here, not sunk past the branch with twice the registers
+#pragma unroll
+                for (int c = 0; c < 3; ++c) __asm__ __volatile__("" : "+v"(em[k - 1][c]));
+            }
+            if (!WARM || j >= 2 * k) collide2d<T>(o, P);  // (uniform)
 #pragma unroll
             for (int pl = 0; pl < 12; ++pl) v[pl] = o[pl];
         }
@@ -682,9 +695,11 @@ __device__ __forceinline__ void xk_row(const T *__restrict__ src, long ps, const
     } else {
         levels(std::false_type{});
     }
+    if constexpr (!WARM) {
 #pragma unroll
-    for (int pl = 0; pl < 12; ++pl) pend[pl] = (T)v[pl];
-    pend_off = ooff;
+        for (int pl = 0; pl < 12; ++pl) pend[pl] = (T)v[pl];
+        pend_off = ooff;
+    }
 }
 
 constexpr int xk_gcd(int a, int b) { return b == 0 ? a : xk_gcd(b, a % b); }
@@ -849,7 +864,44 @@ __device__ __forceinline__ void xk_wave(const T *__restrict__ src, T *__restrict
     unsigned pend_off = kXkDrop;
 #pragma unroll
     for (int pl = 0; pl < 12; ++pl) pend[pl] = (T)0;
-    // PRIO: the row iterations in four quarters (whole unrolled blocks), the issue
+    auto rows_from = [&](int j, auto wc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int jj = j + u;
+            const int orow = y0 - 2 * (K - 1) + jj;
+            // reads from the previous row's parity, writes to this row's
+            const XkLds X{Lp[0].row,     Lp[(u + 1) % 2].r1, Lp[(u + 1) % 2].r3,
+                          Lp[u % 2].w1,  Lp[u % 2].w3,       Lp[(u + 1) % 2].er,
+                          Lp[u % 2].ew1, Lp[u % 2].ew3,      wv};
+            if constexpr (SW > 1) {
+                // every wavefront has written the previous row's edge values;
+                // this row's slots were last read one row ago
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            }
+            const unsigned ooff = (orow >= y0 && orow < y1) ? (unsigned)orow * ostep + lane_off
+                                                            : kXkDrop;
+            rl = rl == ny - 1 ? 0 : rl + 1;
+            ++il;
+            xk_row<T, K, BND, SW, decltype(wc)::value>(
+                src, ps, P, lane, orsrc, ooff, xk_offsets<T>(rl, nx, ny, xm, xw, xp),
+                buf[u % (D + 1)], buf[(u + D) % (D + 1)], e2[u % 2], s1, s3, pend, pend_off, lds, G,
+                B, y0 - (K - 1) + jj, il, xm, xw, xp, bx0, bx1, e2[(u + 1) % 2], X, jj);
+        }
+    };
+    // the rows before the first output (whole unrolled blocks of them)
+    constexpr int WB = 2 * (K - 1) / U;
+    for (int b = 0; b < WB; ++b) {
+        rows_from(b * U, std::true_type{});
+        // keeps the e2 planes in the storage type from block to block (widened, they would
+        // take twice the registers)
+#pragma unroll
+        for (int k = 0; k < K - 1; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) __asm__("" : "+v"(e2[0][k][c]), "+v"(e2[1][k][c]));
+    }
+    // PRIO: the other iterations in four quarters (whole unrolled blocks), the issue
     // priority set before each; otherwise one range
     constexpr int NQ = PRIO ? 4 : 1;
     const int nblk = (niter + U - 1) / U;
@@ -864,35 +916,8 @@ __device__ __forceinline__ void xk_wave(const T *__restrict__ src, T *__restrict
             else
                 __builtin_amdgcn_s_setprio(0);
         }
-        const int jb = nblk * qt / NQ * U, je = nblk * (qt + 1) / NQ * U;
-        for (int j = jb; j < je; j += U) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int jj = j + u;
-                const int orow = y0 - 2 * (K - 1) + jj;
-                // reads from the previous row's parity, writes to this row's
-                const XkLds X{Lp[0].row,        Lp[(u + 1) % 2].r1, Lp[(u + 1) % 2].r3,
-                              Lp[u % 2].w1,     Lp[u % 2].w3,       Lp[(u + 1) % 2].er,
-                              Lp[u % 2].ew1,    Lp[u % 2].ew3,      wv};
-                if constexpr (SW > 1) {
-                    // every wavefront has written the previous row's edge values;
-                    // this row's slots were last read one row ago
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                }
-                const unsigned ooff = (orow >= y0 && orow < y1)
-                                          ? (unsigned)orow * ostep + lane_off
-                                          : kXkDrop;
-                rl = rl == ny - 1 ? 0 : rl + 1;
-                ++il;
-                xk_row<T, K, BND, SW>(src, ps, P, lane, orsrc, ooff,
-                                  xk_offsets<T>(rl, nx, ny, xm, xw, xp), buf[u % (D + 1)],
-                                  buf[(u + D) % (D + 1)], e2[u % 2], s1, s3, pend, pend_off, lds, G,
-                                  B, y0 - (K - 1) + jj, il, xm, xw, xp, bx0, bx1, e2[(u + 1) % 2],
-                                  X);
-            }
-        }
+        const int jb = WB + (nblk - WB) * qt / NQ, je = WB + (nblk - WB) * (qt + 1) / NQ;
+        for (int b = jb; b < je; ++b) rows_from(b * U, std::false_type{});
     }
 #pragma unroll
     for (int pl = 0; pl < 12; ++pl) xk_store(orsrc[pl], pend_off, pend[pl]);
@@ -933,7 +958,8 @@ constexpr int kXkbDefaultKF32 = 8;
 constexpr int kXkbDepth = 1;
 
 // ---- 1D: K steps per launch -------------------------------------------------------
-// A workgroup of NT threads (1024 in the 1D launches, 256 in the persistent
+// (of the batched modes; single grids: line.hip)
+// A workgroup of NT threads (1024 in the flat batched launches, 256 in the persistent
 // batched kernel) holds a tile of NT consecutive nodes in LDS (four planes,
 // double-buffered) and advances it K steps, one node per thread, one barrier per
 // step.  The tile (first node x0) starts K nodes before its NT - 2K output nodes
