@@ -246,6 +246,38 @@ __global__ void __launch_bounds__(512)
     for (int pl = 0; pl < 12; ++pl) sth<2>(o + pl * ps, f[pl]);
 }
 
+// Conserved fields of every instance in one launch over the same units (one launch per
+// instance: 1.7 ms for the 256-instance manifest, 6.6 us each; 0.83 ms so: 2.6 GB of state
+// and 1.35 GB of fields).
+template <typename T>
+__global__ void __launch_bounds__(512)
+    k_batch_moments(const InstDev *__restrict__ inst, const UnitDev *__restrict__ units,
+                    const T *__restrict__ src, double *__restrict__ h, double *__restrict__ qx,
+                    double *__restrict__ qy)
+{
+    const UnitDev ud = units[blockIdx.x];
+    const InstDev &I = inst[ud.inst];
+    const int k = ud.k0 + (int)threadIdx.x;
+    if (k >= I.G.nx * I.G.ny) return;
+    const long ps = I.G.ps, o = I.node + k;
+    const T *s = src + I.off + k;
+    double w[3];
+    if (I.dim == 1) {
+        double f[4];
+#pragma unroll
+        for (int pl = 0; pl < 4; ++pl) f[pl] = ld(s + pl * ps);
+        moments1d(f, w[0], w[1]);
+    } else {
+        double f[12];
+#pragma unroll
+        for (int pl = 0; pl < 12; ++pl) f[pl] = ld(s + pl * ps);
+        moments2d(f, w[0], w[1], w[2]);
+        if (qy) qy[o] = w[2];
+    }
+    if (h) h[o] = w[0];
+    if (qx) qx[o] = w[1];
+}
+
 // ---- step-synchronous mode ------------------------------------------------------------
 // Each step's nodes are cut into units of blockDim consecutive (flat) nodes of
 // one instance, kSyncUnitsPerItem units to a work item; workgroups claim the
@@ -486,17 +518,21 @@ extern "C" void lbm_batch_destroy(lbm_batch *b)
     delete b;
 }
 
-// Rows per 2D segment of the fused mode: one value for every 2D instance, chosen
-// like the single-grid launch (tblock.hip, step2k_seg) -- workgroups run in
-// rounds of the resident slots and each wavefront runs seg + 2 (K - 1) row
-// iterations, so minimise ceil(blocks / slots) * (seg + 2 (K - 1)), a partly
-// filled single round counting proportionally longer.
 static bool inst_bounded(const lbm_instance &I)
 {
     return I.lattice == LBM_D2Q4x3 &&
            !(I.bc[0] == 0 && I.bc[1] == 0 && I.bc[2] == 0 && I.bc[3] == 0);
 }
 
+// Rows per 2D segment of the fused modes, one value for every 2D instance.  A tile runs
+// seg rows and about 10 more to start it (its warm iterations run only the levels that
+// have rows).  Where one round of tiles over the resident slots is the shortest number of
+// rounds, that is taken; else the workgroups take tiles until none is left and wait, half
+// a tile on average, for the last ones:
+//     (all rows + 10 tiles) / slots + (seg + 10) / 2.
+// 40 steps of the 256-instance manifest FP32: 85 rows 11.9 ms, 200 (two whole rounds)
+// 12.1; 64 + 64 instances FP64: 78 rows 9.0, 169 (two rounds) 9.95; 10 + 20 instances: one
+// round of 65 rows 2.6 FP32 and of 129 rows 3.73 FP64, by the second rule 2.7 and 3.82.
 static int fused_seg(bool f32, int K, const std::vector<lbm_instance> &inst, long slots)
 {
     int maxny = 0;
@@ -505,28 +541,36 @@ static int fused_seg(bool f32, int K, const std::vector<lbm_instance> &inst, lon
     if (maxny == 0) return 16;
     if (slots <= 0) return std::min(maxny, 160);
     const int wo = batch_xk_out(f32, K), w = batch_xk_waves(f32, false);
-    const int wob = inst.size() && K <= step2k_max_k_bounded() ? batch_xkb_out(f32, K) : wo;
+    const int wob = K <= step2k_max_k_bounded() ? batch_xkb_out(f32, K) : wo;
     const int wb = batch_xk_waves(f32, true);
-    int best = 0;
-    double best_cost = 0.0;
+    int best = 16, round_best = 16;
+    double best_cost = 0.0, round_cost = 0.0;
+    long round_tiles = 0;
     for (int seg = 16; seg <= maxny; ++seg) {
-        long blocks = 0;
+        double work = 0.0;
+        long tiles = 0;
         for (const lbm_instance &I : inst) {
             if (I.lattice != LBM_D2Q4x3) continue;
             const bool bnd = inst_bounded(I);
             const int o = bnd ? wob : wo, ww = bnd ? wb : w;
             const long groups = ((I.nx + o - 1) / o + ww - 1) / ww;
-            blocks += groups * ((I.ny + seg - 1) / seg);
+            const long nseg = (I.ny + seg - 1) / seg;
+            tiles += groups * nseg;
+            work += (double)groups * (I.ny + 10.0 * nseg);
         }
-        const long rounds = (blocks + slots - 1) / slots;
-        double cost = (double)rounds * (seg + 2 * (K - 1));
-        if (blocks < slots) cost *= (double)slots / (double)blocks;
-        if (best == 0 || cost < best_cost) {
+        const double rc = (double)((tiles + slots - 1) / slots) * (seg + 10.0);
+        if (round_cost == 0.0 || rc < round_cost) {
+            round_best = seg;
+            round_cost = rc;
+            round_tiles = tiles;
+        }
+        const double cost = work / (double)slots + 0.5 * (seg + 10.0);
+        if (best_cost == 0.0 || cost < best_cost) {
             best = seg;
             best_cost = cost;
         }
     }
-    return best;
+    return round_tiles <= slots ? round_best : best;
 }
 
 extern "C" int lbm_batch_create(const lbm_instance *inst_in, int n, int storage, void *f_a,
@@ -602,6 +646,7 @@ extern "C" int lbm_batch_create(const lbm_instance *inst_in, int n, int storage,
         InstDev &d = hi[i];
         d.dim = dim;
         d.off = I.state_offset;
+        d.node = I.node_offset;
         d.G.nx = I.nx;
         d.G.ny = I.ny;
         d.G.ps = round_up((long)I.nx * I.ny, 64);
@@ -1049,16 +1094,14 @@ extern "C" int lbm_batch_check(lbm_batch *b)
 extern "C" int lbm_batch_moments(lbm_batch *b, double *h, double *qx, double *qy)
 {
     if (!b) return bfail(LBM_ESTATE, "null batch");
-    const size_t es = b->f32 ? 4 : 8;
-    for (size_t i = 0; i < b->inst.size(); ++i) {
-        const lbm_instance &I = b->inst[i];
-        const int dim = I.lattice == LBM_D1Q2x2 ? 1 : 2;
-        const void *s = (const char *)b->buf[b->cur] + (size_t)I.state_offset * es;
-        const long no = I.node_offset;
-        BHIP(launch_moments(dim, b->f32, s, h ? h + no : nullptr, qx ? qx + no : nullptr,
-                            (qy && dim == 2) ? qy + no : nullptr, nullptr, b->geo[i], b->st,
-                            nullptr));
-    }
+    const void *s = b->buf[b->cur];
+    if (b->f32)
+        hipLaunchKernelGGL(k_batch_moments<float>, dim3(b->nunits), dim3(b->tune.block), 0, b->st,
+                           b->d_inst, b->d_units, (const float *)s, h, qx, qy);
+    else
+        hipLaunchKernelGGL(k_batch_moments<double>, dim3(b->nunits), dim3(b->tune.block), 0,
+                           b->st, b->d_inst, b->d_units, (const double *)s, h, qx, qy);
+    BHIP(hipGetLastError());
     return LBM_OK;
 }
 

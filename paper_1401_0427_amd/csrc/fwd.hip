@@ -99,18 +99,16 @@ __global__ void __launch_bounds__(256) k_init(int dim, T *__restrict__ dst,
 {
     const long n = (long)G.nx * G.ny;
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double h = h0[i];
-    const double qx = qx0 ? qx0[i] : 0.0;
-    const double qy = (dim == 2 && qy0) ? qy0[i] : 0.0;
+    const bool in = i < n;
+    const double h = in ? h0[i] : 1.0;
+    const double qx = in && qx0 ? qx0[i] : 0.0;
+    const double qy = in && dim == 2 && qy0 ? qy0[i] : 0.0;
     // heights in (2^-500, 2^500): the range in which lbm_rcp is the IEEE quotient
-    if (!(h > 0x1p-500 && h < 0x1p500) || !isfinite(qx) || !isfinite(qy)) {
-        atomicOr(bad, 1);
-        return;
-    }
+    const bool good = h > 0x1p-500 && h < 0x1p500 && isfinite(qx) && isfinite(qy);
+    if (!good) atomicOr(bad, 1);
     const double u = fabs(qx / h), v = fabs(qy / h);
-    const double spd = (u > v ? u : v) + sqrt(P.g * h);
-    atomicMax(speed_bits, (unsigned long long)__double_as_longlong(spd));
+    block_raise(in && good ? (u > v ? u : v) + sqrt(P.g * h) : 0.0, speed_bits);
+    if (!in || !good) return;
     if (dim == 1) {
         double f[4];
         feq1d<T>(h, qx, P, f);

@@ -520,8 +520,8 @@ class Batch:
     def moments(self):
         """Packed (h, qx, qy) float64 device tensors over all instances' nodes."""
         torch = self.torch
-        h = torch.zeros(self.nodes, dtype=torch.float64, device=self.device)
-        qx, qy = torch.zeros_like(h), torch.zeros_like(h)
+        h = torch.empty(self.nodes, dtype=torch.float64, device=self.device)
+        qx, qy = torch.empty_like(h), torch.zeros_like(h)  # (qy of a 1D instance: zero)
         check(load().lbm_batch_moments(self.b, _ptr(h), _ptr(qx), _ptr(qy)), "lbm_batch_moments")
         self.check()
         return h, qx, qy
