@@ -171,8 +171,9 @@ struct lbm_ctx {
     int xk_seg;     // rows per segment of the wave-strip K-step launch
     long xk_slots;  // its resident workgroups on the device
     int xk_seg_k[17];  // rows per segment of a wave-strip launch of k <= fuse steps
-    int rest_seg_k[kMaxFuseRest2d + 1];  // the same for the D2Q5Q4Q4 multi-step launch
-    long rest_slots;                     // its resident workgroups at the full depth
+    int rest_seg_k[kDeepRest2dF32 + 1];  // the same for the D2Q5Q4Q4 multi-step launch
+    long rest_slots;  // its resident workgroups at the full depth
+    int rest_seg;     // and the rows of the plan's segments
 };
 
 // Steps per captured graph: the smallest multiple of twice the steps per launch that is
@@ -217,8 +218,8 @@ static const int kXkMinSeg = 16;
 static const int kMaxFuse2d = 8;
 // D2Q5Q4Q4 on all-periodic grids: steps per launch by default (at most
 // kMaxFuseRest2d); other rest-population grids take one step per launch.
-// Measured at 4096^2 (GLUPS for K = 2 .. 6): FP64 36.6, 56.5, 69.3, 105.1, 102.9;
-// FP32 53.8, 81.9, 102.4, 124.3, 120.6 (one step per launch: 26.9 / 57.5).
+// Measured at 4096^2 (GLUPS for K = 4, 5, 6): FP64 86, 105, 107; FP32 132, 141, 144 (one
+// step per launch: 26.9 / 57.5); 1024^2 FP64 99, 106, 81.
 static const int kDefaultFuseRest2d = 5;
 
 // Steps of one kernel of lbm_step, at most.
@@ -314,15 +315,17 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
         int want = p->fuse_steps;
         c->x2 = allper && !rest;  // two steps per launch: the LDS strip kernel (K = 2)
         c->rest_slots = 0;
-        for (int k = 0; k <= kMaxFuseRest2d; ++k) c->rest_seg_k[k] = 0;
+        c->rest_seg = 0;
+        for (int k = 0; k <= kDeepRest2dF32; ++k) c->rest_seg_k[k] = 0;
         if (rest && dim == 2 && allper) {
             // D2Q5Q4Q4: the multi-step launch at the depth asked for (at most
-            // kMaxFuseRest2d), by default kDefaultFuseRest2d when its launch fills a
-            // third of the device's resident workgroups, else one step per launch
+            // kMaxFuseRest2d), by default kDefaultFuseRest2d when its launch fills the
+            // device (rest2k_fills), else one step per launch
             int k = want ? (want > kMaxFuseRest2d ? kMaxFuseRest2d : want) : kDefaultFuseRest2d;
             long slots = 0;
             const int seg = k >= 2 ? rest2k_seg(c->G, c->f32, k, &slots) : 0;
-            if (k >= 2 && seg > 0 && (want || 3 * rest2k_blocks(c->G, k, seg) >= slots)) {
+            c->rest_seg = seg;
+            if (k >= 2 && seg > 0 && (want || rest2k_fills(c->G, c->f32))) {
                 c->fuse = k;
                 c->rest_slots = slots;
                 for (int kk = 2; kk <= k; ++kk) {
@@ -399,16 +402,22 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     if (p->fuse_steps == 0 && dim == 1) c->merge = line_steps(c->G, rest, c->f32);
     if (p->fuse_steps == 0 && dim == 2) {
         int k = 0;
-        // (a two-step plan is the LDS strip kernel, not a wave-strip one)
-        c->tile = tile2d_plan(c->G, rest, c->f32, c->fuse > 2, &k);
+        // tiles, or wave strips with their own depth and segments where these can run
+        // (all-periodic grids for D2Q5Q4Q4; planes below 2 GiB) and are faster
+        const int deep = rest ? (c->f32 ? kDeepRest2dF32 : kDefaultFuseRest2d)
+                              : step2k_depth(c->G, c->f32, c->fuse);
+        long cols = 0;
+        if ((size_t)c->ps * (c->f32 ? 4 : 8) < ((size_t)1 << 31))
+            cols = !rest ? step2k_cols(c->G, c->f32, deep)
+                   : c->rest_seg > 0 ? rest2k_cols(c->G, c->f32, deep) : 0;
+        c->tile = tile2d_plan(c->G, rest, c->f32, cols, &k);
         if (c->tile >= 0) {
             c->merge = k;
-        } else if (!rest && c->xk_seg > 0) {
-            // wave-strip launches, with their own depth and segments
-            c->merge = c->x2 && !c->f32 ? kXkDeepF64 : c->fuse;
-            for (int k2 = 2; k2 <= c->merge; ++k2) {
-                const int sk = step2k_rows(c->G, c->f32, k2);
-                c->xk_seg_k[k2] = sk > 0 ? sk : c->xk_seg;
+        } else {
+            c->merge = deep;
+            for (int i = 2; i <= deep; ++i) {
+                const int sk = rest ? rest2k_rows(c->G, c->f32, i) : step2k_rows(c->G, c->f32, i);
+                (rest ? c->rest_seg_k : c->xk_seg_k)[i] = sk > 0 ? sk : kXkMinSeg;
             }
         }
     }
@@ -679,7 +688,7 @@ extern "C" int lbm_launch_info(lbm_ctx *c, int *steps_per_launch, int *segment_r
     const bool xk = c->dim == 2 && c->fuse >= 2 && !(c->x2 && c->fuse == 2);
     if (steps_per_launch) *steps_per_launch = c->fuse;
     if (c->rest) {
-        if (segment_rows) *segment_rows = c->fuse >= 2 ? c->rest_seg_k[c->fuse] : 0;
+        if (segment_rows) *segment_rows = c->fuse >= 2 ? c->rest_seg : 0;
         if (resident_blocks) *resident_blocks = c->rest_slots;
         return LBM_OK;
     }

@@ -175,11 +175,15 @@ hipError_t launch_step2x(bool f32, const void *src, void *dst, const Geo &G, con
                          int seg, hipStream_t st);
 int step2k_blocks(const Geo &G, bool f32, int K, int seg);
 int step2k_seg(const Geo &G, bool f32, int K, int min_seg, bool *full, long *slots_out);
-// Depth of the regrouped launches of default plans on all-periodic FP64 grids: 9 steps
-// leave the same 48 output columns of 64 as 8 (16 halo lanes) and take 730 us at 4096^2
-// where 8 take 708 (81 against 88 us a step); 10 leave 40.  FP32: 8 (9 takes the 256-lane
-// strips to two workgroups per compute unit: 62 against 56 us a step).
-constexpr int kXkDeepF64 = 9;
+// Depth of the regrouped launches of default plans (plan: the plan's own).  All-periodic
+// FP64 9: that leaves the same 48 output columns of 64 as 8 (16 halo lanes) and takes 730
+// us at 4096^2 where 8 take 708 (81 against 88 us a step; 10 leave 40); below 1.1 M nodes
+// 7 (760^2 5.6 us a step, 9 steps 6.05; 1200^2 11.7, 11.3).  FP32: the plan's 6 or 8 (9 at
+// 4096^2 takes the 256-lane strips to two workgroups per compute unit, 62 against 56 us);
+// below 800 000 nodes 5 (680^2 4.75, 6 steps 4.9, 8 steps 5.5).  With faces FP64 7, FP32 5
+// below 2 M nodes (1300^2 12.7, 8 steps 14.5), else the plan's.
+int step2k_depth(const Geo &G, bool f32, int plan);
+long step2k_cols(const Geo &G, bool f32, int K);  // columns their whole strips cover
 int step2k_rows(const Geo &G, bool f32, int K);  // segment rows of those launches
 int step2k_max_k_bounded();  // steps per launch at most with non-periodic faces
 int step2k_default_k_bounded(bool f32);  // and by default

@@ -20,10 +20,14 @@
 //   of the second term restored), XX^eq = 0, f_xx^eq = rho u^2 + p,
 //   f_xy^eq = f_yx^eq = rho u v, f_yy^eq = rho v^2 + p.
 // Plane order: rest population first, then the a = 0 order.
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.h"
 #include "rest_device.h"
 #include "xk_wave.h"
 #include "multistep.h"
+#include "strip_device.h"
 
 namespace lbm {
 
@@ -163,104 +167,134 @@ __global__ void __launch_bounds__(256) k_step_rest1d(const T *__restrict__ src, 
 }
 
 // ---- D2Q5Q4Q4, K steps per launch on all-periodic grids ----------------------------
-// One wavefront per column strip of 64 lanes (lane l at column x0 - (K - 1) + l,
-// wrapped), walking down a segment of rows.  Iteration j computes level 1 of row
+// One wavefront per column strip of 64 lanes, walking up a segment of rows, four
+// neighbouring strips to a workgroup.  Iteration j computes level 1 of row
 // i = y0 - (K - 1) + j from the level-n pulls of that row (loaded one iteration
 // ahead), then level k + 1 of row i - k from level k for k = 1 .. K - 1, so the
 // levels are skewed one row apart and only level K leaves the wavefront (row
 // i - (K - 1), stored when it lies in the segment).  Level k + 1 of row r pulls
-// from level k: e1 / e3 of row r from lanes l - 1 / l + 1 (cross-lane, kept from
-// the previous iteration), e2 of row r - 1 (kept two iterations, two arrays used
+// from level k: e1 / e3 of row r from lanes l - 1 / l + 1 (kept from the previous
+// iteration, DPP), e2 of row r - 1 (kept two iterations, two arrays used
 // alternately), e4 of row r + 1 (just computed), and the rest population of row r
 // (kept one iteration).  Every level is rounded to the storage type, as the
 // one-step kernel's store and load round it, and the collision is the same
 // function, so the result equals K single steps bit for bit.  The K - 1 lanes at
-// each strip edge and the first 2 (K - 1) iterations take values from outside the
-// valid range and are not stored.
-template <typename T>
-__device__ __forceinline__ void rest2k_load(const T *__restrict__ src, long ps, int nx, int ny,
-                                            int r, int xm, int xw, int xp, T (&b)[13])
+// each strip edge take values from outside the valid range and are not stored; the
+// first 2 (K - 1) iterations store nothing and skip the collisions of the levels
+// that have no row yet.
+//   A strip owns whole 64-byte pieces of a row (rest2k_out).  All planes share one
+// buffer descriptor where they lie below 2 GiB together (else BIG: one per plane);
+// accesses that must not happen carry an offset the hardware drops, so the loop has
+// no branch and the loads of the next row stay in flight.  Bound by the issue of FP64
+// operations on small grids and by the state through memory from about 2048^2 on.  Two
+// wavefronts fit a SIMD up to K = 5 FP64 (230 registers) and 7 FP32; with 64-bit
+// addresses, permutes and a second row buffer it was one (268): 1024^2 FP64, K = 5, 14.6
+// us a step, 9.9 now, 4096^2 FP32 135, 114 at K = 7; 4096^2 FP64 160 either way (4.4 TB/s).
+template <typename T, int K>
+constexpr int rest2k_out()
 {
-    const long row = (long)r * nx;
-    const long rm = r == 0 ? (long)(ny - 1) * nx : row - nx;
-    const long rp = r == ny - 1 ? 0 : row + nx;
-    b[0] = src[row + xw];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const T *q = src + (1 + 4 * c) * ps;
-        b[1 + 4 * c] = q[row + xm];
-        b[2 + 4 * c] = q[ps + rm + xw];
-        b[3 + 4 * c] = q[2 * ps + row + xp];
-        b[4 + 4 * c] = q[3 * ps + rp + xw];
-    }
+    constexpr int piece = 64 / (int)sizeof(T);
+    return (64 - 2 * (K - 1)) / piece * piece;
 }
 
-template <typename T, int K>
-__global__ void __launch_bounds__(256) k_step_rest2d_k(const T *__restrict__ src,
-                                                       T *__restrict__ dst, Geo G, Mrt M,
-                                                       int nsb, int seg)
+template <typename T, int K, bool BIG>
+__global__ void __launch_bounds__(256, 2)
+    k_step_rest2d_k(const T *__restrict__ src, T *__restrict__ dst, Geo G, Mrt M, int nstrips,
+                    int seg)
 {
-    constexpr int H = K - 1, WO = 64 - 2 * H;
+    constexpr int WO = rest2k_out<T, K>(), H = (64 - WO) / 2;
     const int nx = G.nx, ny = G.ny;
-    const long ps = G.ps;
     const int lane = threadIdx.x & 63;
-    const int strip = (blockIdx.x % nsb) * 4 + (int)(threadIdx.x >> 6);
-    const int y0 = (blockIdx.x / nsb) * seg;
-    if (strip * WO >= nx || y0 >= ny) return;  // whole wavefronts only
-    const int y1 = y0 + seg < ny ? y0 + seg : ny;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform
+    const int ngroups = (nstrips + 3) / 4;
+    const int tile = xk_tile(blockIdx.x, ngroups * ((ny + seg - 1) / seg), true);
+    const int strip = tile % ngroups * 4 + wave;
+    if (strip >= nstrips) return;  // whole wavefront; nothing here waits on others
+    const int y0 = tile / ngroups * seg, y1 = min(y0 + seg, ny);
     const int xc = strip * WO - H + lane;
     const int xw = ((xc % nx) + nx) % nx;
     const int xm = xw == 0 ? nx - 1 : xw - 1, xp = xw == nx - 1 ? 0 : xw + 1;
     const bool olane = lane >= H && lane < H + WO && xc < nx;
-    T e2[2][K - 1][3], s1[K - 1][3], s3[K - 1][3], r0[K - 1];
+    const unsigned sT = sizeof(T), pT = BIG ? 0 : (unsigned)G.ps * sT;  // bytes of a plane
+    auto rsrc = [&](const T *p, int pl) __attribute__((always_inline)) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T *>(BIG ? p + pl * G.ps : p), 0,
+            (int)(BIG ? (unsigned)nx * (unsigned)ny * sT : 13 * pT), 0x00020000);
+    };
+    auto load = [&](int r, T(&b)[13]) __attribute__((always_inline)) {
+        const unsigned row = (unsigned)r * nx, rm = (unsigned)(r == 0 ? ny - 1 : r - 1) * nx,
+                       rp = (unsigned)(r == ny - 1 ? 0 : r + 1) * nx;
+        const unsigned o[4] = {(row + xm) * sT, (rm + xw) * sT, (row + xp) * sT, (rp + xw) * sT};
+        pair_load(rsrc(src, 0), (row + xw) * sT, 0, b[0]);
+#pragma unroll
+        for (int pl = 0; pl < 12; ++pl)
+            pair_load(rsrc(src, 1 + pl), o[pl & 3], (1 + pl) * pT, b[1 + pl]);
+    };
+    T e2[2][K - 1][3], e1[K - 1][3], e3[K - 1][3], r0[K - 1];
 #pragma unroll
     for (int k = 0; k < K - 1; ++k) {
-        r0[k] = (T)0;
+        r0[k] = (T)1;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) e2[0][k][c] = e2[1][k][c] = s1[k][c] = s3[k][c] = (T)0;
+        for (int c = 0; c < 3; ++c) e2[0][k][c] = e2[1][k][c] = e1[k][c] = e3[k][c] = (T)0;
     }
-    const int niter = (y1 - y0) + 2 * H;
-    int rl = (((y0 - H) % ny) + ny) % ny;  // level-1 row of the last load, wrapped
-    T buf[2][13];
-    rest2k_load<T>(src, ps, nx, ny, rl, xm, xw, xp, buf[0]);
-    for (int j = 0; j < niter; j += 2) {
+    T buf[13];
+    int rl = (((y0 - (K - 1)) % ny) + ny) % ny;  // row of the last load, wrapped
+    load(rl, buf);
+    auto row = [&](int j, auto uc, auto wc) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+        constexpr bool WARM = decltype(wc)::value;
+        double v[13];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int orow = y0 - 2 * H + j + u;
-            rl = rl == ny - 1 ? 0 : rl + 1;
-            rest2k_load<T>(src, ps, nx, ny, rl, xm, xw, xp, buf[1 - u]);
-            double v[13];
+        for (int pl = 0; pl < 13; ++pl) v[pl] = (double)buf[pl];
+        __builtin_amdgcn_sched_barrier(0);
+        rl = rl == ny - 1 ? 0 : rl + 1;
+        load(rl, buf);
+        collide_mrt2d(v, M);  // level 1
 #pragma unroll
-            for (int pl = 0; pl < 13; ++pl) v[pl] = (double)buf[u][pl];
-            collide_mrt2d(v, M);  // level 1
+        for (int k = 1; k < K; ++k) {
+            double o[13];
+            o[0] = (double)r0[k - 1];
+            r0[k - 1] = (T)v[0];
 #pragma unroll
-            for (int k = 1; k < K; ++k) {
-#pragma unroll
-                for (int pl = 0; pl < 13; ++pl) v[pl] = (double)(T)v[pl];
-                double o[13];
-                o[0] = (double)r0[k - 1];
-                r0[k - 1] = (T)v[0];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const int b = 1 + 4 * c;
-                    o[b + 0] = (double)s1[k - 1][c];
-                    o[b + 1] = (double)e2[u][k - 1][c];
-                    o[b + 2] = (double)s3[k - 1][c];
-                    o[b + 3] = v[b + 3];
-                    e2[u][k - 1][c] = (T)v[b + 1];
-                    s1[k - 1][c] = xk_xch((T)v[b + 0], lane, 1);
-                    s3[k - 1][c] = xk_xch((T)v[b + 2], lane, -1);
-                }
-                collide_mrt2d(o, M);
-#pragma unroll
-                for (int pl = 0; pl < 13; ++pl) v[pl] = o[pl];
+            for (int c = 0; c < 3; ++c) {
+                const int b = 1 + 4 * c;
+                o[b + 0] = (double)pair_shr(e1[k - 1][c]);
+                o[b + 1] = (double)e2[u][k - 1][c];
+                o[b + 2] = (double)pair_shl(e3[k - 1][c]);
+                o[b + 3] = (double)(T)v[b + 3];
+                e1[k - 1][c] = (T)v[b + 0];
+                e2[u][k - 1][c] = (T)v[b + 1];
+                e3[k - 1][c] = (T)v[b + 2];
             }
-            if (olane && orow >= y0 && orow < y1) {
-                T *q = dst + (long)orow * nx + xc;
+            if constexpr (WARM) {
+                // rounded here, not sunk past the branch with twice the registers
+                __asm__ __volatile__("" : "+v"(r0[k - 1]));
 #pragma unroll
-                for (int pl = 0; pl < 13; ++pl) sth<2>(q + pl * ps, v[pl]);
+                for (int c = 0; c < 3; ++c)
+                    __asm__ __volatile__("" : "+v"(e1[k - 1][c]), "+v"(e2[u][k - 1][c]),
+                                         "+v"(e3[k - 1][c]));
             }
+            __builtin_amdgcn_sched_barrier(0);
+            if (!WARM || j >= 2 * k) collide_mrt2d(o, M);  // (uniform)
+#pragma unroll
+            for (int pl = 0; pl < 13; ++pl) v[pl] = o[pl];
         }
+        if constexpr (!WARM) {
+            const int r = y0 - 2 * (K - 1) + j;
+            const unsigned o = olane && r < y1 ? ((unsigned)r * nx + xc) * sT : kPairDrop;
+#pragma unroll
+            for (int pl = 0; pl < 13; ++pl) pair_store(rsrc(dst, pl), o, pl * pT, (T)v[pl]);
+        }
+    };
+    using std::integral_constant;
+    int j = 0;
+    for (; j < 2 * (K - 1); j += 2) {
+        row(j, integral_constant<int, 0>{}, std::true_type{});
+        row(j + 1, integral_constant<int, 1>{}, std::true_type{});
+    }
+    for (const int n = (y1 - y0) + 2 * (K - 1); j < n; j += 2) {
+        row(j, integral_constant<int, 0>{}, std::false_type{});
+        row(j + 1, integral_constant<int, 1>{}, std::false_type{});
     }
 }
 
@@ -268,30 +302,51 @@ template <typename T, int K>
 static int rest2k_resident()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_step_rest2d_k<T, K>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_step_rest2d_k<T, K, false>, 256, 0) !=
         hipSuccess)
         return 0;
     return nb;
 }
 
-int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out)
+#define LBM_REST_KS(F) F(2) F(3) F(4) F(5) F(6)  // either storage; FP32 7 as well
+// Output columns of a strip.
+static int rest2k_wo(bool f32, int K)
 {
-    int dev = 0, ncu = 0, per = 0;
-    if (slots_out) *slots_out = 0;
+    switch (K) {
+#define LBM_REST_WO(KK) case KK: return f32 ? rest2k_out<float, KK>() : rest2k_out<double, KK>();
+        LBM_REST_KS(LBM_REST_WO)
+#undef LBM_REST_WO
+    case 7: return rest2k_out<float, 7>();
+    default: return 0;
+    }
+}
+
+// Workgroups of the K-step launch resident per compute unit, compute units (0: unknown).
+static int rest2k_per_cu(bool f32, int K, int *ncu)
+{
+    int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        hipDeviceGetAttribute(ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
     switch (K) {
 #define LBM_REST_OCC(KK) \
-    case KK: per = f32 ? rest2k_resident<float, KK>() : rest2k_resident<double, KK>(); break;
-        LBM_REST_OCC(2) LBM_REST_OCC(3) LBM_REST_OCC(4) LBM_REST_OCC(5) LBM_REST_OCC(6)
+    case KK: return f32 ? rest2k_resident<float, KK>() : rest2k_resident<double, KK>();
+        LBM_REST_KS(LBM_REST_OCC)
 #undef LBM_REST_OCC
+    case 7: return f32 ? rest2k_resident<float, 7>() : 0;
     default: return 0;
     }
+}
+
+int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out)
+{
+    int ncu = 0;
+    if (slots_out) *slots_out = 0;
+    const int per = rest2k_per_cu(f32, K, &ncu);
     const long slots = (long)ncu * per;
     if (slots_out) *slots_out = slots;
     if (slots <= 0) return 0;
-    const int WO = 64 - 2 * (K - 1);
+    const int WO = rest2k_wo(f32, K);
     const long ngroups = ((G.nx + WO - 1) / WO + 3) / 4;
     // segment length of the fewest rows computed per wavefront over whole rounds of
     // resident workgroups (halo rows: 2 (K - 1) per segment)
@@ -313,35 +368,92 @@ int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out)
     return best;
 }
 
-long rest2k_blocks(const Geo &G, int K, int seg)
+long rest2k_cols(const Geo &G, bool f32, int K)
 {
-    const int WO = 64 - 2 * (K - 1);
+    const long wo = rest2k_wo(f32, K);
+    return ((G.nx + wo - 1) / wo + 3) / 4 * 4 * wo;
+}
+
+bool rest2k_fills(const Geo &G, bool f32)
+{
+    int ncu = 0;
+    if (rest2k_per_cu(f32, 5, &ncu) <= 0) return false;
+    int nseg = 1;  // most segments of at least kRestMinSeg rows
+    for (int n = 2; n <= G.ny; ++n) {
+        const int sg = (G.ny + n - 1) / n;
+        if (sg < kRestMinSeg) break;
+        if ((G.ny + sg - 1) / sg == n) nseg = n;
+    }
+    return 3L * (((G.nx + 55) / 56 + 3) / 4) * nseg >= (f32 ? 2L : 1L) * ncu;
+}
+
+// Rows per segment for the regrouped launches of default plans: an iteration of two
+// workgroups on a compute unit takes 1.97 times that of one (4096^2 FP64, 5 steps: 4.95
+// and 2.47 us), so a second one only shortens the tail; the start of a segment costs 1.3
+// iterations per level.  1024^2 FP64, 5 steps: 49 segments of 21 rows (one workgroup
+// each) 9.9 us a step, 64 of 16 (two on some) 13.0.
+int rest2k_rows(const Geo &G, bool f32, int K)
+{
+    int ncu = 0;
+    const int per = std::min(rest2k_per_cu(f32, K, &ncu), 2);
+    if (per <= 0) return 0;
+    const int WO = rest2k_wo(f32, K);
+    const long ngroups = ((G.nx + WO - 1) / WO + 3) / 4;
+    static const double kIter[3] = {0.0, 1.0, 1.97};
+    int best = 0;
+    double best_cost = 0.0;
+    for (int nseg = 1; nseg <= G.ny; ++nseg) {
+        const int sg = (G.ny + nseg - 1) / nseg;
+        if (sg < 8 && nseg > 1) break;
+        if ((G.ny + sg - 1) / sg != nseg) continue;
+        const long n = (ngroups * nseg + ncu - 1) / ncu;
+        const double cost =
+            ((double)(n / per) * kIter[per] + kIter[n % per]) * (sg + 1.3 * K);
+        if (best == 0 || cost < best_cost) {
+            best = sg;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+static long rest2k_blocks(const Geo &G, bool f32, int K, int seg)
+{
+    const int WO = rest2k_wo(f32, K);
     return (long)(((G.nx + WO - 1) / WO + 3) / 4) * ((G.ny + seg - 1) / seg);
+}
+
+template <typename T, int K>
+static hipError_t rest2k_launch(const void *src, void *dst, const Geo &G, const Mrt &M, int seg,
+                                hipStream_t st)
+{
+    constexpr int WO = rest2k_out<T, K>();
+    const int ns = (G.nx + WO - 1) / WO;
+    const dim3 grid((unsigned)rest2k_blocks(G, sizeof(T) == 4, K, seg)), block(256);
+    if (13L * G.ps * (long)sizeof(T) < (1L << 31))
+        hipLaunchKernelGGL((k_step_rest2d_k<T, K, false>), grid, block, 0, st, (const T *)src,
+                           (T *)dst, G, M, ns, seg);
+    else
+        hipLaunchKernelGGL((k_step_rest2d_k<T, K, true>), grid, block, 0, st, (const T *)src,
+                           (T *)dst, G, M, ns, seg);
+    return hipGetLastError();
 }
 
 hipError_t launch_step_rest2k(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
                               int K, int seg, hipStream_t st)
 {
     if (seg <= 0) return hipErrorInvalidValue;
-    const int WO = 64 - 2 * (K - 1);
-    const int nsb = ((G.nx + WO - 1) / WO + 3) / 4;
-    const dim3 grid((unsigned)rest2k_blocks(G, K, seg)), block(256);
     switch (K) {
 #define LBM_REST_K(KK)                                                                       \
     case KK:                                                                                 \
-        if (f32)                                                                             \
-            hipLaunchKernelGGL((k_step_rest2d_k<float, KK>), grid, block, 0, st,            \
-                               (const float *)src, (float *)dst, G, M, nsb, seg);            \
-        else                                                                                 \
-            hipLaunchKernelGGL((k_step_rest2d_k<double, KK>), grid, block, 0, st,           \
-                               (const double *)src, (double *)dst, G, M, nsb, seg);          \
-        break;
-        LBM_REST_K(2) LBM_REST_K(3) LBM_REST_K(4) LBM_REST_K(5) LBM_REST_K(6)
+        return f32 ? rest2k_launch<float, KK>(src, dst, G, M, seg, st)                       \
+                   : rest2k_launch<double, KK>(src, dst, G, M, seg, st);
+        LBM_REST_KS(LBM_REST_K)
 #undef LBM_REST_K
+    case 7: return f32 ? rest2k_launch<float, 7>(src, dst, G, M, seg, st) : hipErrorInvalidValue;
     default:
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // f*(0) = C(f^eq(W0)) with the same checks as the a = 0 initialisation.
@@ -354,17 +466,15 @@ __global__ void __launch_bounds__(256) k_init_rest(int dim, T *__restrict__ dst,
 {
     const long n = (long)G.nx * G.ny;
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const double h = h0[i];
-    const double qx = qx0 ? qx0[i] : 0.0;
-    const double qy = (dim == 2 && qy0) ? qy0[i] : 0.0;
-    if (!(h > 0.0) || !isfinite(h) || !isfinite(qx) || !isfinite(qy)) {
-        atomicOr(bad, 1);
-        return;
-    }
+    const bool in = i < n;
+    const double h = in ? h0[i] : 1.0;
+    const double qx = in && qx0 ? qx0[i] : 0.0;
+    const double qy = in && dim == 2 && qy0 ? qy0[i] : 0.0;
+    const bool good = h > 0.0 && isfinite(h) && isfinite(qx) && isfinite(qy);
+    if (!good) atomicOr(bad, 1);
     const double u = fabs(qx / h), v = fabs(qy / h);
-    const double spd = (u > v ? u : v) + sqrt(M.g * h);
-    atomicMax(speed_bits, (unsigned long long)__double_as_longlong(spd));
+    block_raise(in && good ? (u > v ? u : v) + sqrt(M.g * h) : 0.0, speed_bits);
+    if (!in || !good) return;
     if (dim == 1) {
         double f[5];
         feq_rest1d(h, qx, M, f);

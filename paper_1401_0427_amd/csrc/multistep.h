@@ -9,11 +9,18 @@ namespace lbm {
 // (one wavefront per 64-column strip, four to a 256-thread workgroup, segments of
 // `seg` rows; bitwise equal to K single steps).  rest2k_seg: the segment length
 // for the device's resident workgroups (0 if it cannot be queried), slots_out the
-// resident workgroups; rest2k_blocks: workgroups of one launch.
+// resident workgroups; rest2k_fills: whether default plans take it, segments of 16 rows
+// giving a third of a workgroup (FP32: two thirds) per compute unit.
 constexpr int kMaxFuseRest2d = 6;
+// Depth of the regrouped launches of default FP32 plans (us a step at 2048^2 and 4096^2
+// for 5, 6, 7, 8 steps: 33.3, 32.1, 32.5, 33.1 and 119, 117, 114, 113); FP64 keeps the
+// plan's 5 (1024^2: 9.9, 6 steps 12.9; 4096^2: 160, 156; from 6 on it spills registers).
+constexpr int kDeepRest2dF32 = 7;
+int rest2k_rows(const Geo &G, bool f32, int K);  // segment rows of those launches
+long rest2k_cols(const Geo &G, bool f32, int K);  // columns their whole strips cover
 constexpr int kRestMinSeg = 16;
 int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out);
-long rest2k_blocks(const Geo &G, int K, int seg);
+bool rest2k_fills(const Geo &G, bool f32);
 hipError_t launch_step_rest2k(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
                               int K, int seg, hipStream_t st);
 // 1D (D1Q2 per component; D1Q3Q2), K steps per launch with the nodes in registers
@@ -28,8 +35,9 @@ int line_steps(const Geo &G, bool rest, bool f32);
 
 // 2D grids, K steps per launch of register tiles (csrc/tile2d.hip), any faces; bitwise
 // equal to K single steps.  tile2d_plan: the tile shape and the steps per launch for a
-// grid, or -1 where the wave-strip launches (strips: they fill the device) are faster.
-int tile2d_plan(const Geo &G, bool rest, bool f32, bool strips, int *K);
+// grid, or -1 where the wave-strip launches, whose whole strips cover strip_cols columns
+// (0: there are none), are faster.
+int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K);
 hipError_t launch_tile2d(bool f32, int shape, const void *src, void *dst, const Geo &G,
                          const Phys &P, int K, hipStream_t st);
 hipError_t launch_tile2d_rest(bool f32, int shape, const void *src, void *dst, const Geo &G,

@@ -292,6 +292,23 @@ int step2k_blocks(const Geo &G, bool f32, int K, int seg)
     return ngroups * ((G.ny + seg - 1) / seg);
 }
 
+long step2k_cols(const Geo &G, bool f32, int K)
+{
+    const bool bnd = geo_bounded(G);
+    const int sw = bnd ? 1 : f32 ? xk_sw<float>() : xk_sw<double>();
+    return (long)step2k_groups(G, f32, K) * (sw > 1 ? 1 : kXkWaves) * xk_wo_of(f32, K, bnd, sw);
+}
+
+int step2k_depth(const Geo &G, bool f32, int plan)
+{
+    const long nodes = (long)G.nx * G.ny;
+    if (!geo_bounded(G)) {
+        if (f32) return nodes < 800000 ? 5 : plan > 2 ? plan : 6;
+        return nodes < 1100000 ? 7 : 9;
+    }
+    if (f32) return nodes < 2000000 ? 5 : plan > 2 ? plan : 8;
+    return 7;
+}
 
 int step2k_max_k_bounded() { return kXkMaxKBnd; }
 int step2k_default_k_bounded(bool f32)

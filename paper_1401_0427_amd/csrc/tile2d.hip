@@ -284,15 +284,16 @@ static double tile_cost(const Geo &G, bool rest, bool f32, bool bnd, const TileS
 // wall / Neumann faces against one step per launch, at 35 x 20, 70 x 40, 140 x 80,
 // 280 x 160, 560 x 320: 0.94 / 4.75, 1.03 / 4.2, 1.34 / 4.3, 2.1 / 5.6, 3.9 / 8.9; all
 // periodic 0.80 / 2.7, 0.93 / 2.9, 1.2 / 3.1, 1.9 / 4.4, 3.4 / 8.9).  On larger grids
-// the wave-strip launches take over where they fill the device (`strips`): us per step
-// tile / strip at 717 000 and 1 050 000 nodes FP64 periodic 8.7 / 9.8, 14.5 / 13.7, with
-// faces 9.7 / 12, 16.2 / 16.2; FP32 periodic 6.9 / 7.9, 9.3 / 11.2 (1.8 M: 14.6 / 13.0),
-// with faces 7.9 / 11.9, 11.0 / 16.2 (1.8 M: 17.6 / 19.0, 2.1 M: 19.6 / 19.2); MRT
-// periodic FP64 10.9 / 11.4, 17.0 / 14.6, FP32 10.0 / 10.1, 13.7 / 15.6 (1.8 M: 22 /
-// 19).  MRT with faces has no strip launch: tiles throughout (4.2 M nodes FP64 71 us
-// against 163 for one step per launch).  The limits count the nodes of whole output
-// tiles, so narrow grids that tiles cover badly leave earlier.
-int tile2d_plan(const Geo &G, bool rest, bool f32, bool strips, int *K)
+// the wave-strip launches take over (us a step tile / strips on square grids: periodic
+// FP64 250 000 nodes 4.2 / 4.6, 302 000 5.3 / 4.6, 577 000 8.4 / 5.6; FP32 360 000 4.4 /
+// 4.7, 462 000 5.2 / 4.8, 883 000 8.2 / 6.9; with faces FP64 462 000 7.7 / 8.5, 722 000
+// 11.0 / 10.8, FP32 1.05 M 11.0 / 11.9, 1.7 M 15.6 / 12.7; MRT periodic FP64 202 000 4.4 /
+// 4.8, 302 000 6.2 / 4.9, 722 000 12.0 / 7.1, FP32 360 000 6.2 / 6.4, 577 000 9.0 / 7.1).
+// MRT with faces has no strip launch: tiles throughout (4.2 M nodes FP64 71 us against
+// 163 for one step per launch).  The limits count the nodes of whole output tiles, and
+// grow with the columns that whole strips cover beyond the grid's (200 x 2000 FP64: 5.9 /
+// 6.5; 2000 x 200: 6.0 / 5.1).  strip_cols: those columns, 0 where no strip launch runs.
+int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K)
 {
     const bool bnd = G.bc[0] != BC_PERIODIC || G.bc[2] != BC_PERIODIC;
     const long nodes = (long)G.nx * G.ny;
@@ -322,11 +323,13 @@ int tile2d_plan(const Geo &G, bool rest, bool f32, bool strips, int *K)
             *K = k;
         }
     }
-    if (strips) {
+    if (strip_cols > 0) {
         const long wo = S.tx - 2 * *K, ho = S.ty * S.R - 2 * *K;
         const long covered = (G.nx + wo - 1) / wo * wo * ((G.ny + ho - 1) / ho * ho);
-        const long limit = f32 ? (bnd ? 1900000 : 1300000) : (bnd ? 950000 : rest ? 800000 : 850000);
-        if (covered > limit) return -1;
+        const long limit = rest ? (f32 ? 520000 : 270000)
+                           : bnd ? (f32 ? 1500000 : 640000)
+                                 : (f32 ? 450000 : 300000);
+        if ((double)covered > (double)limit * strip_cols / (1.1 * G.nx)) return -1;
     }
     return shape;
 }
