@@ -258,8 +258,8 @@ struct TileShape {
     int resident;  // tiles per compute unit (registers)
 };
 static const TileShape kTileShapes[] = {
-    {16, 16, 1, 8}, {32, 16, 1, 4}, {32, 16, 2, 2}, {64, 8, 4, 1}, {32, 8, 4, 3}};
-enum { kTile16 = 0, kTile32x16, kTile32, kTile64x32, kTile32Tall };
+    {16, 16, 1, 8}, {32, 16, 1, 4}, {32, 16, 2, 2}, {64, 8, 3, 1}, {64, 8, 4, 1}, {32, 8, 4, 3}};
+enum { kTile16 = 0, kTile32x16, kTile32, kTile64x24, kTile64x32, kTile32Tall };
 
 // Microseconds per step of a K-step launch: its fixed cost, the state through the
 // caches, and K steps of either one tile's latency or the issue of the tiles that share
@@ -283,7 +283,10 @@ static double tile_cost(const Geo &G, bool rest, bool f32, bool bnd, const TileS
 // Shape by the number of nodes (measured fastest, us per step FP64 a = 0 with inflow /
 // wall / Neumann faces against one step per launch, at 35 x 20, 70 x 40, 140 x 80,
 // 280 x 160, 560 x 320: 0.94 / 4.75, 1.03 / 4.2, 1.34 / 4.3, 2.1 / 5.6, 3.9 / 8.9; all
-// periodic 0.80 / 2.7, 0.93 / 2.9, 1.2 / 3.1, 1.9 / 4.4, 3.4 / 8.9).  On larger grids
+// periodic 0.80 / 2.7, 0.93 / 2.9, 1.2 / 3.1, 1.9 / 4.4, 3.4 / 8.9).  What changes at a
+// limit is how many tiles fall on the fullest compute unit: 400 x 300 with faces in tiles
+// of 64 x 24 FP64 2.7, FP32 2.5, of 64 x 32 (at a smaller depth) 3.3, 3.0; 160 x 140 in
+// 32 x 16 1.5, in 32 x 32 1.9; 640 x 600 in 32 x 32 tall 6.1, in 64 x 32 7.1.  On larger grids
 // the wave-strip launches take over (us a step tile / strips on square grids: periodic
 // FP64 250 000 nodes 4.2 / 4.6, 302 000 5.3 / 4.6, 577 000 8.4 / 5.6; FP32 360 000 4.4 /
 // 4.7, 462 000 5.2 / 4.8, 883 000 8.2 / 6.9; with faces FP64 462 000 7.7 / 8.5, 722 000
@@ -300,11 +303,13 @@ int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K)
     int shape, lo = 2, hi = 10;
     if (nodes < 5000) {
         shape = kTile16;
-    } else if (nodes < 22000) {
+    } else if (nodes < (bnd || rest ? 30000 : 23500)) {
         shape = kTile32x16;
-    } else if (nodes < 90000) {
+    } else if (nodes < (f32 && !rest && bnd ? 108000 : 90000)) {
         shape = kTile32;
-    } else if (nodes < 400000) {
+    } else if (nodes < 150000 && !(f32 && !rest && !bnd && nodes < 112000)) {
+        shape = kTile64x24;
+    } else if (nodes < (!bnd ? 400000 : f32 ? 300000 : rest ? 400000 : 330000)) {
         shape = kTile64x32;
     } else if (f32) {
         shape = bnd ? kTile32 : kTile64x32;
@@ -360,6 +365,7 @@ static hipError_t tile_any(int shape, const void *src, void *dst, const Geo &G, 
     case kTile16: return tile_launch<T, PH, false, 16, 16, 1>(src, dst, 0, G, P, K, st);
     case kTile32x16: return tile_launch<T, PH, false, 32, 16, 1>(src, dst, 0, G, P, K, st);
     case kTile32: return tile_launch<T, PH, false, 32, 16, 2>(src, dst, 0, G, P, K, st);
+    case kTile64x24: return tile_launch<T, PH, false, 64, 8, 3>(src, dst, 0, G, P, K, st);
     case kTile64x32: return tile_launch<T, PH, false, 64, 8, 4>(src, dst, 0, G, P, K, st);
     case kTile32Tall:
         if constexpr (sizeof(T) == 8)

@@ -34,7 +34,7 @@ def test_tile_launches_equal_single_steps(faces, rest, storage):
     import torch
 
     for nx, ny in ((2, 2), (3, 5), (16, 7), (70, 71), (71, 71), (148, 148), (149, 149),
-                   (2, 4000), (5000, 3), (300, 299), (301, 299), (633, 631), (640, 640),
+                   (2, 4000), (5000, 3), (300, 299), (301, 299), (301, 300), (391, 383), (570, 575), (633, 631), (640, 640),
                    (1300, 700)):
         steps = 37 if nx * ny < 100000 else 21
         A = _solver(nx, ny, FACES[faces], rest, storage, 1)
