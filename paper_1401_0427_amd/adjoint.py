@@ -100,6 +100,8 @@ def rollout(h0: torch.Tensor, s: torch.Tensor, T: int, K: int | None = None, lam
     state storage)."""
     if K is None:
         K = max(1, int(round(math.sqrt(T))))
+        if K > 6:
+            K = (K + 2) // 4 * 4  # segments of whole two-step launches, in even numbers
     return _Rollout.apply(h0, s, int(T), int(K), float(lam), float(g), storage, int(block),
                           adjoint_storage, tuple(bc), inflow)
 
