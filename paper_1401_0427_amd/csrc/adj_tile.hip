@@ -15,6 +15,8 @@
 // level of u and lambda is rounded to its storage type and dL/ds is summed in the same
 // groups and order as by the one-step kernel, so the result is bitwise that of one-step
 // launches over every level.
+#include <type_traits>
+
 #include "adj_device.h"
 #include "multistep.h"
 #include "strip_device.h"
@@ -169,17 +171,19 @@ __global__ void __launch_bounds__(TX * TY)
 // per workgroup, 1.8 times the nodes: 36 us a step at 1024^2 FP32), and the loads of the
 // next row overlap the arithmetic of this one.  Between iterations a lane keeps the e1,
 // e3 and (two rows) e2 planes of u^{n+1}, the e1, e3 and (two rows) e4 planes of
-// vt^{n+1}, and in LDS its own v^n of the last three rows.  Stores and partial sums are
+// vt^{n+1}, and in LDS its own v^n of the last three rows.  The first iterations run only
+// the stages that have rows (two of four, then two of two more: 10 % of a segment of 20
+// rows).  Stores and partial sums are
 // buffer accesses whose non-owned lanes carry a dropped offset, so the loop has no
 // branch, and a row's partial sums are read one iteration ahead like its planes: read
 // in the iteration that needs them, behind the next row's loads, they made it wait for
 // those (1024^2 FP32 28.4 us a step, 24.5 ahead).  Stages are kept apart by scheduling
 // barriers so that two wavefronts fit a SIMD without spills (FP64 82 us a step spilling,
 // 40 without), and all planes share one buffer descriptor (a descriptor and a base per
-// plane spilled 38 scalar registers).  At 1024^2 21.3 us a step FP32 (one-step kernel
-// 31.2), FP64 35.2 (60.0); 2048^2 84 (123) and 149 (229): u^n, lambda and their halos at
-// 4.0 TB/s.  48 owned columns, whole 64-byte pieces, lose at 1024^2 (23.1, 38.9) what
-// they gain at 2048^2 (83.5, 147.6).
+// plane spilled 38 scalar registers).  At 1024^2 19.3 us a step FP32 (one-step kernel
+// 31.2), FP64 34.6 (60.0); 2048^2 77 (123) and 145 (229): u^n, lambda and their halos at
+// 4.0 TB/s.  48 owned columns, whole 64-byte pieces, lose at 1024^2 (8 %) what they gain
+// at 2048^2 (1 %).
 constexpr int kPairWaves = 4;  // wavefronts (neighbouring strips) per workgroup
 constexpr int kPairOut = 56;   // columns a strip owns
 
@@ -242,47 +246,48 @@ __global__ void __launch_bounds__(64 * kPairWaves, 2)
     T ub[12];
     TA lb[12];
     double pnext = 0.0;
-    int ru = wrap(y0 - 2), rl = wrap(y0 - 3);  // rows of the last loads
+    int ru = wrap(y0 - 2), rl = wrap(y0 - 1);  // rows of the last loads
     load_u(ru, ub);
     load_l(rl, lb);
     int h0 = 0;  // slot of v^n of row i
     double sprev = 0.0;
-    const int niter = (y1 - y0) + 4;
-    for (int j = 0; j < niter; j += 2) {
+    // Iteration j in stages: u^{n+1} at row i; step n + 1 at row i - 1, which has no row
+    // that anything needs before j = 2; step n at row i - 2, none before j = 4.
+    auto row = [&](int j, auto qc, auto stages) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, S = decltype(stages)::value;
+        const int i = y0 - 2 + j;  // row of v^n
+        const int r0 = i - 2;      // row of step n
+        const bool out = ox && r0 < y1;
+        const double pold = pnext;
+        const unsigned po = lead && r0 < y1 ? (unsigned)r0 * prow + pcol : kPairDrop;
+        // level n at row i: u^{n+1}
+        double v[12];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int i = y0 - 2 + j + q;  // row of v^n
-            const int r0 = i - 2;          // row of step n
-            const bool out = ox && r0 >= y0 && r0 < y1;
-            const double pold = pnext;
-            const unsigned po = lead && r0 >= y0 && r0 < y1 ? (unsigned)r0 * prow + pcol : kPairDrop;
-            // level n at row i: u^{n+1}
-            double v[12];
+        for (int pl = 0; pl < 12; ++pl) {
+            v[pl] = (double)ub[pl];
+            H[h0][pl][lane] = ub[pl];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        ru = ru == ny - 1 ? 0 : ru + 1;
+        load_u(ru, ub);
+        pair_load(rp,
+                  lead && r0 + 1 >= y0 && r0 + 1 < y1 ? (unsigned)(r0 + 1) * prow + pcol : kPairDrop,
+                  0, pnext);
+        collide2d<T>(v, P);
+        // v^{n+1} at row i - 1
+        double w[12];
 #pragma unroll
-            for (int pl = 0; pl < 12; ++pl) {
-                v[pl] = (double)ub[pl];
-                H[h0][pl][lane] = ub[pl];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            ru = ru == ny - 1 ? 0 : ru + 1;
-            load_u(ru, ub);
-            pair_load(rp,
-                      lead && r0 + 1 >= y0 && r0 + 1 < y1 ? (unsigned)(r0 + 1) * prow + pcol
-                                                          : kPairDrop,
-                      0, pnext);
-            collide2d<T>(v, P);
-            // v^{n+1} at row i - 1
-            double w[12];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                w[4 * c + 0] = (double)pair_shr(u1e1[c]);
-                w[4 * c + 1] = (double)u1e2[q][c];
-                w[4 * c + 2] = (double)pair_shl(u1e3[c]);
-                w[4 * c + 3] = (double)(T)v[4 * c + 3];
-                u1e1[c] = (T)v[4 * c + 0];
-                u1e2[q][c] = (T)v[4 * c + 1];
-                u1e3[c] = (T)v[4 * c + 2];
-            }
+        for (int c = 0; c < 3; ++c) {
+            w[4 * c + 0] = (double)pair_shr(u1e1[c]);
+            w[4 * c + 1] = (double)u1e2[q][c];
+            w[4 * c + 2] = (double)pair_shl(u1e3[c]);
+            w[4 * c + 3] = (double)(T)v[4 * c + 3];
+            u1e1[c] = (T)v[4 * c + 0];
+            u1e2[q][c] = (T)v[4 * c + 1];
+            u1e3[c] = (T)v[4 * c + 2];
+        }
+        h0 = h0 == 2 ? 0 : h0 + 1;  // also the slot of row i - 2
+        if constexpr (S >= 2) {
             double l[12];
 #pragma unroll
             for (int pl = 0; pl < 12; ++pl) l[pl] = (double)lb[pl];
@@ -304,35 +309,49 @@ __global__ void __launch_bounds__(64 * kPairWaves, 2)
                 te3[c] = n3;
                 te4[q][c] = n4;
             }
-            h0 = h0 == 2 ? 0 : h0 + 1;  // also the slot of row i - 2
+            if constexpr (S >= 3) {
 #pragma unroll
-            for (int pl = 0; pl < 12; ++pl) w[pl] = (double)H[h0][pl][lane];
-            __builtin_amdgcn_sched_barrier(0);
-            const double a0 = adj_node2d<T>(w, l, P);
-            const double s0 = group_sum(ox ? a0 : 0.0);
-            const unsigned row = (unsigned)r0 * nx;
-            const unsigned rm = (unsigned)(r0 == 0 ? ny - 1 : r0 - 1) * nx;
-            const unsigned rq = (unsigned)(r0 == ny - 1 ? 0 : r0 + 1) * nx;
-            const unsigned o1 = out ? (row + xm) * sA : kPairDrop;
-            const unsigned o2 = out ? (rm + xw) * sA : kPairDrop;
-            const unsigned o3 = out ? (row + xp) * sA : kPairDrop;
-            const unsigned o4 = out ? (rq + xw) * sA : kPairDrop;
+                for (int pl = 0; pl < 12; ++pl) w[pl] = (double)H[h0][pl][lane];
+                __builtin_amdgcn_sched_barrier(0);
+                const double a0 = adj_node2d<T>(w, l, P);
+                const double s0 = group_sum(ox ? a0 : 0.0);
+                const unsigned row = (unsigned)r0 * nx;
+                const unsigned rm = (unsigned)(r0 == 0 ? ny - 1 : r0 - 1) * nx;
+                const unsigned rq = (unsigned)(r0 == ny - 1 ? 0 : r0 + 1) * nx;
+                const unsigned o1 = out ? (row + xm) * sA : kPairDrop;
+                const unsigned o2 = out ? (rm + xw) * sA : kPairDrop;
+                const unsigned o3 = out ? (row + xp) * sA : kPairDrop;
+                const unsigned o4 = out ? (rq + xw) * sA : kPairDrop;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                pair_store(rs, o1, (4 * c + 0) * pA, (TA)l[4 * c + 0]);
-                pair_store(rs, o2, (4 * c + 1) * pA, (TA)l[4 * c + 1]);
-                pair_store(rs, o3, (4 * c + 2) * pA, (TA)l[4 * c + 2]);
-                pair_store(rs, o4, (4 * c + 3) * pA, (TA)l[4 * c + 3]);
+                for (int c = 0; c < 3; ++c) {
+                    pair_store(rs, o1, (4 * c + 0) * pA, (TA)l[4 * c + 0]);
+                    pair_store(rs, o2, (4 * c + 1) * pA, (TA)l[4 * c + 1]);
+                    pair_store(rs, o3, (4 * c + 2) * pA, (TA)l[4 * c + 2]);
+                    pair_store(rs, o4, (4 * c + 3) * pA, (TA)l[4 * c + 3]);
+                }
+                pair_store(rp, po, 0, (pold + sprev) + s0);
             }
-            pair_store(rp, po, 0, (pold + sprev) + s0);
             sprev = s1;
         }
+    };
+    using std::integral_constant;
+    const integral_constant<int, 0> even{};
+    const integral_constant<int, 1> odd{};
+    row(0, even, integral_constant<int, 1>{});
+    row(1, odd, integral_constant<int, 1>{});
+    row(2, even, integral_constant<int, 2>{});
+    row(3, odd, integral_constant<int, 2>{});
+    for (int j = 4, n = (y1 - y0) + 4; j < n; j += 2) {
+        row(j, even, integral_constant<int, 3>{});
+        row(j + 1, odd, integral_constant<int, 3>{});
     }
 }
 
-// Rows per segment: a wavefront runs seg + extra iterations (start included) of about 1.55 us with one workgroup per compute unit and 2.55 us with two (fitted at
-// six sizes), in rounds of these; the shortest such time.  A few workgroups beyond a
-// round cost it whole: 260 instead of 245 at 1024^2 took 47 us a launch instead of 43.
+// Rows per segment: a wavefront runs seg rows and `extra` iterations more (its start), an
+// iteration taking 1.92 times as long with two workgroups on a compute unit as with one
+// (1024^2 FP32: 2.8 and 1.6 us, 2048^2 4.0 and 1.9), in rounds of these; the shortest such
+// time.  A few workgroups beyond a round cost it whole: 260 instead of 245 at 1024^2 took
+// 47 us a launch instead of 43.
 static int strip_seg(const Geo &G, int nstrips, int extra)
 {
     int best = G.ny;
@@ -341,7 +360,7 @@ static int strip_seg(const Geo &G, int nstrips, int extra)
         const long waves = (long)nstrips * ((G.ny + seg - 1) / seg);
         const long blocks = (waves + kPairWaves - 1) / kPairWaves;
         const double it = seg + extra;
-        const double t = blocks <= 256 ? 1.55 * it : 2.55 * it * (double)((blocks + 511) / 512);
+        const double t = blocks <= 256 ? it : 1.92 * it * (double)((blocks + 511) / 512);
         if (t < cost) {
             cost = t;
             best = seg;
@@ -355,7 +374,7 @@ static hipError_t strip_launch(const void *un, const void *lam2, void *lam0, dou
                                const Geo &G, const Phys &P, hipStream_t st)
 {
     const int ns = (G.nx + kPairOut - 1) / kPairOut;
-    const int seg = strip_seg(G, ns, 6);
+    const int seg = strip_seg(G, ns, 4);
     const long waves = (long)ns * ((G.ny + seg - 1) / seg);
     hipLaunchKernelGGL((k_adj2d_strip<T, TA>), dim3((waves + kPairWaves - 1) / kPairWaves),
                        dim3(64 * kPairWaves), 0, st, (const T *)un, (const TA *)lam2, (TA *)lam0,
@@ -381,7 +400,7 @@ hipError_t launch_adjoint_pair(bool f32, bool a32, const void *un, const void *l
 }
 
 // Steps per launch over stored levels, by nodes; 0: two-step launches from every second
-// level are faster (512^2 FP64: 12.5 us a step there, 13.9 here; 724^2 FP32 12.8, 16.5).
+// level are faster (512^2 FP64: 12.5 us a step there, 13.9 here; 724^2 FP32 11.5, 16.5).
 int adjoint_levels_steps(const Geo &G)
 {
     const long nodes = (long)G.nx * G.ny;
