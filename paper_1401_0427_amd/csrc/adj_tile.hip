@@ -61,8 +61,7 @@ __device__ __forceinline__ void pair_push(T (&l)[R][12], PairRows<T, N> &B, int 
 // (j - 1) * stride), lambda stays in registers.  A step loses one more row and column at
 // the tile's edges; nodes at least 4 columns and K - 1 rows inside are exact and owned.
 // Bound by the latency of a launch and of a step's chain of operations: 96 x 64 FP64
-// 1.8 us a step against 4.2 for one step per launch, 256^2 4.4 against 6.1, 512^2 12.5
-// against 16.2.
+// 1.8 us a step against 4.2 for one step per launch, 256^2 4.4 against 6.1.
 template <typename T, typename TA, int TX, int TY, int R>
 __global__ void __launch_bounds__(TX * TY)
     k_adj2d_levels(const T *__restrict__ first, const T *__restrict__ next, long stride,
@@ -400,11 +399,15 @@ hipError_t launch_adjoint_pair(bool f32, bool a32, const void *un, const void *l
 }
 
 // Steps per launch over stored levels, by nodes; 0: two-step launches from every second
-// level are faster (512^2 FP64: 12.5 us a step there, 13.9 here; 724^2 FP32 11.5, 16.5).
+// level are faster.  Us a step FP32 / FP64 at 200^2, 256^2, 300^2, 350^2, 400^2, 512^2: 3
+// steps 2.7 / 3.2, 3.6 / 4.6, 5.0 / 7.1, 5.8 / 7.7, 6.4 / 8.6, 8.9 / 12.8; 5 steps 2.3 /
+// 2.9, 4.1 / 5.6, 4.7 / 6.6, 4.9 / 6.6, 7.4 / 10.6, 10.0 / 14.7 (what changes is how many
+// tiles fall on a compute unit); in strips 5.5 / 6.7, 5.9 / 6.8, 6.1 / 7.3, 6.0 / 7.8, 6.4
+// / 8.6, 7.8 / 10.9.
 int adjoint_levels_steps(const Geo &G)
 {
     const long nodes = (long)G.nx * G.ny;
-    return nodes <= 50000 ? 5 : nodes <= 300000 ? 3 : 0;
+    return nodes > 140000 ? 0 : nodes > 50000 && nodes <= 75000 ? 3 : 5;
 }
 
 template <typename T, typename TA, int TX, int TY, int R>
@@ -421,8 +424,8 @@ static hipError_t levels_launch(const void *first, const void *next, long stride
     return hipGetLastError();
 }
 
-// Tiles grow with the grid: 16^2 keeps 6000 nodes on 100 compute units, 64 x 16 loses
-// least to halos (fastest of seven shapes at each size).
+// Tiles grow with the grid: 16^2 keeps 6000 nodes on 100 compute units, 32^2 loses least
+// to halos (fastest of seven shapes at each size).
 template <typename T, typename TA>
 static hipError_t levels_any(const void *first, const void *next, long stride, const void *lamK,
                              void *lam0, double *partials, const Geo &G, const Phys &P, int K,
@@ -435,10 +438,7 @@ static hipError_t levels_any(const void *first, const void *next, long stride, c
     if (nodes <= 100000)
         return levels_launch<T, TA, 32, 16, 1>(first, next, stride, lamK, lam0, partials, G, P, K,
                                                st);
-    if (nodes <= 200000)
-        return levels_launch<T, TA, 32, 16, 2>(first, next, stride, lamK, lam0, partials, G, P, K,
-                                               st);
-    return levels_launch<T, TA, 64, 8, 2>(first, next, stride, lamK, lam0, partials, G, P, K, st);
+    return levels_launch<T, TA, 32, 16, 2>(first, next, stride, lamK, lam0, partials, G, P, K, st);
 }
 
 hipError_t launch_adjoint_levels(bool f32, bool a32, const void *first, const void *next,

@@ -10,11 +10,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("storage,adj", [("f64", None), ("f32", "f32"), ("f32", "f64")])
-@pytest.mark.parametrize("nx,ny", [(2, 2), (3, 7), (57, 16), (109, 110), (110, 110), (223, 224),
-                                   (316, 317), (450, 444), (547, 548), (548, 548), (56, 6000),
+@pytest.mark.parametrize("nx,ny", [(2, 2), (3, 7), (57, 16), (109, 110), (110, 110), (223, 224), (250, 251),
+                                   (316, 317), (370, 375), (450, 444), (547, 548), (548, 548), (56, 6000),
                                    (6001, 57), (840, 834), (1450, 1400)])
 def test_sweeps_equal_single_steps(nx, ny, storage, adj):
-    """The first and last sizes of every shape (tiles of 16^2 .. 64 x 16 nodes, strips of 56
+    """The first and last sizes of every shape (tiles of 16^2 .. 32^2 nodes, strips of 56
     and 48 columns with a ragged last one and uneven segments), grids smaller than a tile, and
     segment lengths with every remainder."""
     import torch
