@@ -126,9 +126,8 @@ typedef struct {
                              grids above.  lbm_launch_info reports the choice.
                              With 0, lbm_step may run the steps of several
                              launches of the plan in one kernel, or those of one
-                             launch in several, where that is faster (1D, and
-                             2D grids too small for the deep launches); a depth
-                             asked for is kept. */
+                             launch in several, and choose other segments, where
+                             that is faster; a depth asked for is kept. */
     void *f_a, *f_b;      /* caller-owned device state buffers (ping-pong) */
     void *stream;         /* hipStream_t; NULL = default stream */
     int adjoint_storage;  /* element type of adjoint buffers: 0 = the state's,

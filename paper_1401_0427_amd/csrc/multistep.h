@@ -1,5 +1,5 @@
-// Multi-step launches of the rest-population lattices (csrc/mrt.hip), outside the
-// hot path's wave-strip kernels.
+// Multi-step launches beside the wave strips of the a = 0 scheme (tblock.hip): 1D in
+// registers, register tiles, the rest-population strips and the adjoint sweeps.
 #pragma once
 #include "internal.h"
 
