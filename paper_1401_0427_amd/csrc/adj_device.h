@@ -6,11 +6,12 @@
 
 namespace lbm {
 
-// mu = J^T l at W = (h, qx, qy), J = d f^eq / d W.
-__device__ __forceinline__ void adj_mu(const double *l, double h, double qx, double qy,
+// mu = J^T l at W = (h, qx, qy), J = d f^eq / d W; ih = 1 / h.  The adjoint steps take
+// lbm_rcp(h), which their f^eq has computed already; the gradient at a caller's W0, whose
+// heights nothing has checked, the division.
+__device__ __forceinline__ void adj_mu(const double *l, double h, double ih, double qx, double qy,
                                        const Phys &P, double &mh, double &mx, double &my)
 {
-    const double ih = lbm_rcp(h);
     const double u = qx * ih, v = qy * ih, gh = P.g * h;
     const double L0h = (l[0] + l[2]) + (l[1] + l[3]);
     const double Lxh = l[0] - l[2], Lyh = l[1] - l[3];
@@ -32,7 +33,7 @@ __device__ __forceinline__ double adj_node2d(const double *v, double *l, const P
     double h, qx, qy, e[12], mu[3];
     moments2d(v, h, qx, qy);
     feq2d<T>(h, qx, qy, P, e);
-    adj_mu(l, h, qx, qy, P, mu[0], mu[1], mu[2]);
+    adj_mu(l, h, lbm_rcp(h), qx, qy, P, mu[0], mu[1], mu[2]);
     double acc[3] = {0.0, 0.0, 0.0};  // one chain per component
 #pragma unroll
     for (int pl = 0; pl < 12; ++pl)

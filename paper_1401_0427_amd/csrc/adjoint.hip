@@ -153,10 +153,10 @@ __global__ void __launch_bounds__(256) k_adj2d_bnd(const T *__restrict__ un,
 // (Sec. 2 potentials) give
 //   mu_h = (L_f+ + L_f-) / 2 + c (g h - u^2) (L_g+ - L_g-)
 //   mu_q = c (L_f+ - L_f-) + (L_g+ + L_g-) / 2 + 2 u c (L_g+ - L_g-)
-__device__ __forceinline__ void adj_mu1d(const double *l, double h, double q, const Phys &P,
-                                         double &mh, double &mq)
+__device__ __forceinline__ void adj_mu1d(const double *l, double h, double ih, double q,
+                                         const Phys &P, double &mh, double &mq)
 {
-    const double u = q * lbm_rcp(h);
+    const double u = q * ih;
     const double L1g = l[2] - l[3];
     mh = 0.5 * (l[0] + l[1]) + P.c * (P.g * h - u * u) * L1g;
     mq = P.c * (l[0] - l[1]) + 0.5 * (l[2] + l[3]) + 2.0 * u * P.c * L1g;
@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(256) k_adj1d(const T *__restrict__ un,
         double h, q, e[4], mu[2];
         moments1d(v, h, q);
         feq1d<T>(h, q, P, e);
-        adj_mu1d(l, h, q, P, mu[0], mu[1]);
+        adj_mu1d(l, h, lbm_rcp(h), q, P, mu[0], mu[1]);
 #pragma unroll
         for (int pl = 0; pl < 4; ++pl) acc += l[pl] * (e[pl] - v[pl]);
         const double oms = 1.0 - P.s;
@@ -281,11 +281,12 @@ __global__ void __launch_bounds__(256) k_adj_grad_w0(const T *__restrict__ lam0,
     const long n = (long)G.nx * G.ny;
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
+    const double h = h0[i], ih = 1.0 / h;
     if (dim == 1) {
         double l[4], mh, mq;
 #pragma unroll
         for (int pl = 0; pl < 4; ++pl) l[pl] = ld(lam0 + pl * G.ps + i);
-        adj_mu1d(l, h0[i], qx0 ? qx0[i] : 0.0, P, mh, mq);
+        adj_mu1d(l, h, ih, qx0 ? qx0[i] : 0.0, P, mh, mq);
         if (gh) gh[i] = mh;
         if (gqx) gqx[i] = mq;
         return;
@@ -294,7 +295,7 @@ __global__ void __launch_bounds__(256) k_adj_grad_w0(const T *__restrict__ lam0,
 #pragma unroll
     for (int pl = 0; pl < 12; ++pl) l[pl] = ld(lam0 + pl * G.ps + i);
     double mh, mx, my;
-    adj_mu(l, h0[i], qx0 ? qx0[i] : 0.0, qy0 ? qy0[i] : 0.0, P, mh, mx, my);
+    adj_mu(l, h, ih, qx0 ? qx0[i] : 0.0, qy0 ? qy0[i] : 0.0, P, mh, mx, my);
     if (gh) gh[i] = mh;
     if (gqx) gqx[i] = mx;
     if (gqy) gqy[i] = my;
