@@ -144,8 +144,10 @@ int lbm_layout(const lbm_params *p, long *plane_stride, int *n_planes, size_t *b
  * initial conserved fields (Sec. 2: f^eq from the kinetic potentials; Sec. 3 for
  * 2D).  h0, qx0, qy0: device double arrays of nx*ny values row-major [y][x]
  * (qx0 / qy0 may be NULL for zero; qy0 ignored in 1D).
- * Synchronises the stream once to check min h0 > 0 (else LBM_EINVAL) and the
- * monotonicity bound (LBM_WARN_SUBCHAR, context still created). */
+ * Synchronises the stream once to check min h0 > 0 (else LBM_EINVAL; a = 0 lattices:
+ * heights between 2^-500 and 2^500) and the monotonicity bound (LBM_WARN_SUBCHAR, context
+ * still created).  Rest-population lattices whose heights or g lie outside that range run
+ * one step per launch. */
 int lbm_init(const lbm_params *p, const double *h0, const double *qx0, const double *qy0,
              lbm_ctx **out);
 

@@ -139,6 +139,7 @@ struct lbm_ctx {
     lbm_params p;
     int dim;
     bool rest;  // rest-population scheme (D1Q3Q2 / D2Q5Q4Q4, MRT)
+    bool wide;  // of it: g, a prescribed or an initial height outside kRestRange
     Mrt M;
     bool f32;
     bool a32;  // adjoint buffers hold floats (else doubles)
@@ -421,10 +422,6 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
             }
         }
     }
-    // regrouped kernels run long enough to be launched one by one
-    c->chunk_len =
-        c->merge > 0 ? 0 : 2 * c->fuse * ((kChunk + 2 * c->fuse - 1) / (2 * c->fuse));
-
     hipError_t e;
     const int nmb = moments_blocks(c->G);
     if ((e = hipMalloc(&c->d_speed, sizeof(unsigned long long))) != hipSuccess ||
@@ -458,11 +455,25 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
         lbm_destroy(c);
         return fail(LBM_EDEVICE, "initialisation failed: %s", hipGetErrorString(e));
     }
-    if (bad) {
+    if (bad & 1) {
         lbm_destroy(c);
-        return fail(LBM_EINVAL, "initial fields need finite values and 2^-500 < h < 2^500 "
-                                 "everywhere");
+        return fail(LBM_EINVAL, "initial fields need finite values and %s everywhere",
+                    rest ? "h > 0" : "2^-500 < h < 2^500");
     }
+    if (rest) {
+        const auto out_of_range = [](double v) { return !(v > 1.0 / kRestRange && v < kRestRange); };
+        c->wide = (bad & 2) || out_of_range(p->g);
+        for (int f = 0; f < (dim == 1 ? 2 : 4); ++f)
+            c->wide = c->wide || (p->bc[f] == LBM_BC_INFLOW && out_of_range(p->inflow[f][0]));
+        if (c->wide) {  // one step per launch, with plain divisions
+            c->fuse = 1;
+            c->merge = 0;
+            c->tile = -1;
+        }
+    }
+    // regrouped kernels run long enough to be launched one by one
+    c->chunk_len =
+        c->merge > 0 ? 0 : 2 * c->fuse * ((kChunk + 2 * c->fuse - 1) / (2 * c->fuse));
     *out = c;
     double speed;
     memcpy(&speed, &speed_bits, sizeof speed);
@@ -477,7 +488,7 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
 
 static hipError_t step_once(lbm_ctx *c, const void *src, void *dst, hipStream_t st)
 {
-    if (c->rest) return launch_step_rest(c->dim, c->f32, src, dst, c->G, c->M, st);
+    if (c->rest) return launch_step_rest(c->dim, c->f32, c->wide, src, dst, c->G, c->M, st);
     return launch_step(c->dim, c->f32, src, dst, c->G, c->P, c->L, st);
 }
 

@@ -15,6 +15,9 @@ struct Mrt {
     double g, hg, c;  // g, g / 2, 1 / (2 lambda)
     double rate[10];  // relaxation rates of the non-conserved moments
 };
+// Initial and prescribed heights and g between its inverse and this run the fast divisions
+// of the collisions (rest_device.h); others, one step per launch with plain ones.
+constexpr double kRestRange = 0x1p500;
 
 // One instance of the batched form: geometry, physics and the element offset of
 // its planes in the batch buffers.
@@ -220,7 +223,7 @@ hipError_t launch_entropy(int dim, bool f32, const void *state, const Geo &G, do
 hipError_t launch_init_rest(int dim, bool f32, void *dst, const double *h0, const double *qx0,
                             const double *qy0, const Geo &G, const Mrt &M,
                             unsigned long long *speed_bits, int *bad, hipStream_t st);
-hipError_t launch_step_rest(int dim, bool f32, const void *src, void *dst, const Geo &G,
+hipError_t launch_step_rest(int dim, bool f32, bool wide, const void *src, void *dst, const Geo &G,
                             const Mrt &M, hipStream_t st);
 hipError_t launch_moments_rest(int dim, bool f32, const void *state, double *h, double *qx,
                                double *qy, double *partials, int *flag, const Geo &G,

@@ -61,7 +61,7 @@ struct Phys {
 // the residual -- the steps of the full division sequence without its operand
 // scaling and special-case fix-up, which leave such h unchanged (checked
 // against the IEEE quotient on 2^32 values spread over that range, all equal).
-// lbm_init rejects initial heights outside the range.
+// lbm_init rejects initial heights outside the range for the a = 0 lattices.
 __device__ __forceinline__ double lbm_rcp(double h)
 {
     double r = __builtin_amdgcn_rcp(h);

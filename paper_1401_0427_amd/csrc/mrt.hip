@@ -122,7 +122,8 @@ __device__ double pull_rest_face1d(const T *__restrict__ src, const Geo &G, cons
 }
 
 // ---- kernels -------------------------------------------------------------------------
-template <typename T>
+// WIDE: any heights and g (rest_device.h).
+template <typename T, bool WIDE>
 __global__ void __launch_bounds__(256) k_step_rest2d(const T *__restrict__ src, T *__restrict__ dst,
                                                      Geo G, Mrt M, int tiles_x, int allper)
 {
@@ -132,13 +133,13 @@ __global__ void __launch_bounds__(256) k_step_rest2d(const T *__restrict__ src, 
     if (x >= G.nx) return;
     double f[13];
     pull_rest2d(src, G, M, allper != 0, x, y, f);
-    collide_mrt2d(f, M);
+    collide_mrt2d<WIDE>(f, M);
     T *o = dst + (long)y * G.nx + x;
 #pragma unroll
     for (int pl = 0; pl < 13; ++pl) sth<2>(o + pl * G.ps, f[pl]);
 }
 
-template <typename T>
+template <typename T, bool WIDE>
 __global__ void __launch_bounds__(256) k_step_rest1d(const T *__restrict__ src, T *__restrict__ dst,
                                                      Geo G, Mrt M)
 {
@@ -161,7 +162,7 @@ __global__ void __launch_bounds__(256) k_step_rest1d(const T *__restrict__ src, 
         f[2] = pull_rest_face1d(src, G, M, 2, 1, x);
         f[4] = pull_rest_face1d(src, G, M, 4, 1, x);
     }
-    collide_mrt1d(f, M);
+    collide_mrt1d<WIDE>(f, M);
 #pragma unroll
     for (int pl = 0; pl < 5; ++pl) sth<2>(dst + pl * ps + x, f[pl]);
 }
@@ -456,7 +457,8 @@ hipError_t launch_step_rest2k(bool f32, const void *src, void *dst, const Geo &G
     }
 }
 
-// f*(0) = C(f^eq(W0)) with the same checks as the a = 0 initialisation.
+// f*(0) = C(f^eq(W0)).  bad: bit 0 for a field that is refused, bit 1 for a height outside
+// kRestRange.
 template <typename T>
 __global__ void __launch_bounds__(256) k_init_rest(int dim, T *__restrict__ dst,
                                                    const double *__restrict__ h0,
@@ -472,19 +474,20 @@ __global__ void __launch_bounds__(256) k_init_rest(int dim, T *__restrict__ dst,
     const double qy = in && dim == 2 && qy0 ? qy0[i] : 0.0;
     const bool good = h > 0.0 && isfinite(h) && isfinite(qx) && isfinite(qy);
     if (!good) atomicOr(bad, 1);
+    if (!(h > 1.0 / kRestRange && h < kRestRange)) atomicOr(bad, 2);
     const double u = fabs(qx / h), v = fabs(qy / h);
     block_raise(in && good ? (u > v ? u : v) + sqrt(M.g * h) : 0.0, speed_bits);
     if (!in || !good) return;
     if (dim == 1) {
         double f[5];
         feq_rest1d(h, qx, M, f);
-        collide_mrt1d(f, M);
+        collide_mrt1d<true>(f, M);
 #pragma unroll
         for (int pl = 0; pl < 5; ++pl) st(dst + pl * G.ps + i, f[pl]);
     } else {
         double f[13];
         feq_rest2d(h, qx, qy, M, f);
-        collide_mrt2d(f, M);
+        collide_mrt2d<true>(f, M);
 #pragma unroll
         for (int pl = 0; pl < 13; ++pl) st(dst + pl * G.ps + i, f[pl]);
     }
@@ -551,28 +554,30 @@ hipError_t launch_init_rest(int dim, bool f32, void *dst, const double *h0, cons
     return hipGetLastError();
 }
 
-hipError_t launch_step_rest(int dim, bool f32, const void *src, void *dst, const Geo &G,
-                            const Mrt &M, hipStream_t st)
+template <typename T, bool WIDE>
+static void step_rest(int dim, const void *src, void *dst, const Geo &G, const Mrt &M,
+                      hipStream_t st)
 {
-    if (dim == 2) {
-        const int tiles_x = (G.nx + 255) / 256;
-        const int allper = G.bc[0] == BC_PERIODIC && G.bc[1] == BC_PERIODIC &&
-                           G.bc[2] == BC_PERIODIC && G.bc[3] == BC_PERIODIC;
-        if (f32)
-            hipLaunchKernelGGL(k_step_rest2d<float>, dim3(tiles_x * G.ny), dim3(256), 0, st,
-                               (const float *)src, (float *)dst, G, M, tiles_x, allper);
-        else
-            hipLaunchKernelGGL(k_step_rest2d<double>, dim3(tiles_x * G.ny), dim3(256), 0, st,
-                               (const double *)src, (double *)dst, G, M, tiles_x, allper);
-    } else {
-        const int nb = (G.nx + 255) / 256;
-        if (f32)
-            hipLaunchKernelGGL(k_step_rest1d<float>, dim3(nb), dim3(256), 0, st,
-                               (const float *)src, (float *)dst, G, M);
-        else
-            hipLaunchKernelGGL(k_step_rest1d<double>, dim3(nb), dim3(256), 0, st,
-                               (const double *)src, (double *)dst, G, M);
-    }
+    const int tiles_x = (G.nx + 255) / 256;
+    const int allper = G.bc[0] == BC_PERIODIC && G.bc[1] == BC_PERIODIC &&
+                       G.bc[2] == BC_PERIODIC && G.bc[3] == BC_PERIODIC;
+    if (dim == 2)
+        hipLaunchKernelGGL((k_step_rest2d<T, WIDE>), dim3(tiles_x * G.ny), dim3(256), 0, st,
+                           (const T *)src, (T *)dst, G, M, tiles_x, allper);
+    else
+        hipLaunchKernelGGL((k_step_rest1d<T, WIDE>), dim3(tiles_x), dim3(256), 0, st,
+                           (const T *)src, (T *)dst, G, M);
+}
+
+hipError_t launch_step_rest(int dim, bool f32, bool wide, const void *src, void *dst,
+                            const Geo &G, const Mrt &M, hipStream_t st)
+{
+    if (f32)
+        wide ? step_rest<float, true>(dim, src, dst, G, M, st)
+             : step_rest<float, false>(dim, src, dst, G, M, st);
+    else
+        wide ? step_rest<double, true>(dim, src, dst, G, M, st)
+             : step_rest<double, false>(dim, src, dst, G, M, st);
     return hipGetLastError();
 }
 

@@ -11,7 +11,10 @@ namespace lbm {
 // product is within an ulp of the quotient, and one correction with its exact
 // residual rounds to the quotient (Markstein's division).  3 operations more than
 // the reciprocal, against 10 and a scaling test for the full division sequence,
-// and one reciprocal serves every quotient by b.
+// and one reciprocal serves every quotient by b.  The residual is exact for |a| >=
+// 2^-1010; a smaller one counts for nothing in a state whose heights and g lie within
+// kRestRange (its quotient is below 2^-510 there, squared or times a momentum zero).
+// Beyond that range, the contexts run the WIDE collisions, with plain divisions.
 __device__ __forceinline__ double div_by(double a, double b, double rb)
 {
     const double q = a * rb;
@@ -51,6 +54,7 @@ __device__ __forceinline__ void feq_rest2d(double h, double qx, double qy, const
     e[9] = yq + Fxy * M.c; e[10] = yq + Fyy * M.c; e[11] = yq - Fxy * M.c; e[12] = yq - Fyy * M.c;
 }
 
+template <bool WIDE = false>
 __device__ __forceinline__ void collide_mrt1d(double *f, const Mrt &M)
 {
     const double lam = M.lam, il = M.il;
@@ -60,13 +64,14 @@ __device__ __forceinline__ void collide_mrt1d(double *f, const Mrt &M)
     double eps = (lam * lam) * (sp - 2.0 * f[0]);
     const double q = f[3] + f[4];
     double Jq = lam * (f[3] - f[4]);
-    const double u = div_by(q, rho, lbm_rcp(rho));
+    const double u = WIDE ? q / rho : div_by(q, rho, lbm_rcp(rho));
     const double p = M.hg * (rho * rho);
     const double theta = M.g * rho - 0.5 * (u * u);
     J += M.rate[0] * (q - J);
     eps += M.rate[1] * ((lam * lam) * (rho - 3.0 * (M.aK * theta)) - eps);
     Jq += M.rate[2] * ((q * u + p) - Jq);
-    const double f0 = div_by(rho - eps * (il * il), 3.0, 1.0 / 3.0);
+    const double r3 = rho - eps * (il * il);
+    const double f0 = WIDE ? r3 / 3.0 : div_by(r3, 3.0, 1.0 / 3.0);
     const double S = rho - f0;
     f[0] = f0;
     f[1] = 0.5 * (S + J * il);
@@ -96,6 +101,7 @@ __device__ __forceinline__ void fam_invert(double *g, double il, double q, doubl
     g[3] = 0.5 * (b - my * il);
 }
 
+template <bool WIDE = false>
 __device__ __forceinline__ void collide_mrt2d(double *f, const Mrt &M)
 {
     const double lam = M.lam, il = M.il;
@@ -109,12 +115,14 @@ __device__ __forceinline__ void collide_mrt2d(double *f, const Mrt &M)
     double qx, fxx, fxy, XXu, qy, fyx, fyy, XXv;
     fam_moments(f + 5, lam, qx, fxx, fxy, XXu);
     fam_moments(f + 9, lam, qy, fyx, fyy, XXv);
-    const double ir = lbm_rcp(rho);
+    const double ir = WIDE ? 1.0 / rho : lbm_rcp(rho);
     const double u = qx * ir, v = qy * ir;
     const double p = M.hg * (rho * rho);
     Jx += r[0] * (qx - Jx);
     Jy += r[1] * (qy - Jy);
-    eps += r[2] * (((1.0 - 2.5 * M.a) * rho + div_by((1.25 * M.a) * (u * u + v * v), M.g, lbm_rcp(M.g))) - eps);
+    const double k2 = (1.25 * M.a) * (u * u + v * v);
+    const double kg = WIDE ? k2 / M.g : div_by(k2, M.g, lbm_rcp(M.g));
+    eps += r[2] * (((1.0 - 2.5 * M.a) * rho + kg) - eps);
     XX += r[3] * (0.0 - XX);
     fxx += r[4] * ((qx * u + p) - fxx);
     fxy += r[5] * (qx * v - fxy);
