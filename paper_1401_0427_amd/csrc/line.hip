@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "line_plan.h"
 #include "rest_device.h"
 #include "xk_wave.h"
 #include "multistep.h"
@@ -329,74 +330,11 @@ __global__ void __launch_bounds__(64 * W)
     }
 }
 
-// ---- launchers -----------------------------------------------------------------------
-// Output nodes per tile of a K-step launch with R nodes per lane (a multiple of R;
-// <= 0: the halo does not leave any).
-static int line_out(int K, int R) { return (64 * R - (K + R - 1) / R * R - K) / R * R; }
-
-// Nodes per lane the tiled launch is built for, and the wavefronts per SIMD resident
-// with each (registers).
-static const struct {
-    int R, waves;
-} kLineShapes[] = {{2, 6}, {3, 4}, {4, 4}, {6, 3}, {7, 3}, {10, 2}};
-
-// Microseconds per step of a K-step tiled launch.  A launch costs about 4.5 us (its
-// start, and the load and store phases of one tile) plus the state at 5 TB/s, which
-// nothing overlaps: all wavefronts load, step and store together.  A step takes a
-// wavefront a + b R on its own (the chain of dependent FP64 operations of a node,
-// then issue), or c R per wavefront on its SIMD once these fill it.  a, b, c fitted to
-// 8 shapes x 7 depths at 7 sizes from 2000 to 2^20 nodes: the shape and depth it picks
-// were the fastest measured, or within 2 % of it, at each size.
-static double line_cost(int nx, bool rest, bool f32, int K, int R, int waves)
-{
-    const int nout = line_out(K, R);
-    if (nout <= 0) return 1e30;
-    const long tiles = (nx + nout - 1) / nout;
-    long w = (tiles + 1023) / 1024;  // wavefronts per SIMD (256 CUs x 4 SIMDs)
-    if (w > waves) w = (tiles + 1024L * waves - 1) / (1024L * waves) * waves;  // rounds
-    const double a = rest ? 0.08 : 0.09, b = rest ? 0.117 : 0.065, c = rest ? 0.117 : 0.070;
-    const double one = a + b * R, all = (double)w * c * R;
-    const double bytes = (double)nx * (rest ? 10 : 8) * (f32 ? 4 : 8);
-    return (4.5 + bytes / 5e6 + K * (one > all ? one : all)) / K;
-}
-
-static int line_shape(int nx, bool rest, bool f32, int K, double *cost)
-{
-    int R = 0;
-    double best = 1e30;
-    for (const auto &s : kLineShapes) {
-        const double t = line_cost(nx, rest, f32, K, s.R, s.waves);
-        if (t < best) {
-            best = t;
-            R = s.R;
-        }
-    }
-    if (cost) *cost = best;
-    return R;
-}
-
-// At most this many steps per tiled launch (beyond it halos outgrow the tiles: no
-// size measured faster at 128 than at 96).
-constexpr int kLineMaxK = 96;
-// A domain with non-periodic ends of at most this many nodes runs in one workgroup
-// for any number of steps: one wavefront takes 0.16 / 0.26 us a step with 1 / 2 nodes
-// per lane, four 0.33 us, against 0.31 us (0.41 with a rest population) for 48-step
-// launches of tiles; sixteen wavefronts (1024 nodes on one compute unit) 0.52 us.
-constexpr int kLineWholeNodes = 256;
-
+// ---- launchers (shapes and depths: line_plan.h) ---------------------------------------
 int line_steps(const Geo &G, bool rest, bool f32)
 {
     if (step1k_whole(G) && G.nx <= kLineWholeNodes) return 0;
-    int K = 16;
-    double best = 1e30, t;
-    for (int k = 16; k <= kLineMaxK; k += 16) {
-        line_shape(G.nx, rest, f32, k, &t);
-        if (t < best) {
-            best = t;
-            K = k;
-        }
-    }
-    return K;
+    return line_depth(G.nx, G.bc[0] == BC_PERIODIC, rest, f32);
 }
 
 template <typename T, int R, typename PH>
@@ -434,7 +372,7 @@ static hipError_t line_launch(const void *src, void *dst, const Geo &G, const PH
             whole_launch<T, 1, 16>(src, dst, G, P, K, st);
         return hipGetLastError();
     }
-    switch (line_shape(G.nx, kRest<PH>, sizeof(T) == 4, K, nullptr)) {
+    switch (line_shape(G.nx, G.bc[0] == BC_PERIODIC, kRest<PH>, sizeof(T) == 4, K, nullptr)) {
     case 2: tile_launch<T, 2>(src, dst, G, P, K, st); break;
     case 3: tile_launch<T, 3>(src, dst, G, P, K, st); break;
     case 4: tile_launch<T, 4>(src, dst, G, P, K, st); break;
