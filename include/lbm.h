@@ -188,6 +188,30 @@ int lbm_launch_info(lbm_ctx *ctx, int *steps_per_launch, int *segment_rows,
  * nsteps < 0, cap < 0, or cap > 0 with ks NULL. */
 int lbm_launch_plan(lbm_ctx *ctx, long nsteps, int *ks, int cap, long *n_launches);
 
+/* The kernel launches that a call issues, in order: with run = LBM_RUN_STEP those of
+ * lbm_step(ctx, nsteps) from the current step count, regrouped ones as they run (equal to
+ * lbm_launch_plan where a depth was asked for); LBM_RUN_LEVELS those of lbm_step_levels(ctx,
+ * .., nsteps, ..); LBM_RUN_ADJOINT the sweep of lbm_adjoint_levels over nsteps levels.
+ * launches[i] for i < min(number, cap); *n_launches = the number (may be NULL).  The calls
+ * themselves walk the same list (the schemes of Sec. 2 and Sec. 3; the launches of a plan
+ * do not change the state).  No device work.  LBM_EINVAL for another run, nsteps < 0, cap <
+ * 0, cap > 0 with launches NULL, or LBM_RUN_ADJOINT on a context without an adjoint. */
+enum { LBM_RUN_STEP = 0, LBM_RUN_LEVELS = 1, LBM_RUN_ADJOINT = 2 };
+enum {
+    LBM_K_STEP = 1,  /* one step */
+    LBM_K_LDS2 = 2,  /* two steps, strips in LDS */
+    LBM_K_STRIP = 3, /* wavefronts marching up column strips, `rows` rows each */
+    LBM_K_TILE = 4,  /* register tiles of cols x rows nodes */
+    LBM_K_LINE = 5   /* 1D register tiles of cols nodes (rows = 1) */
+};
+typedef struct {
+    int kernel; /* LBM_K_* */
+    int steps;
+    int cols, rows; /* as above, else 0 */
+} lbm_launch;
+int lbm_run_plan(lbm_ctx *ctx, int run, long nsteps, lbm_launch *launches, int cap,
+                 long *n_launches);
+
 /* Copy the current state to dst / overwrite it from src (device, same layout). */
 int lbm_export(lbm_ctx *ctx, void *dst);
 int lbm_import(lbm_ctx *ctx, const void *src);

@@ -373,7 +373,7 @@ static hipError_t strip_launch(const void *un, const void *lam2, void *lam0, dou
                                const Geo &G, const Phys &P, hipStream_t st)
 {
     const int ns = (G.nx + kPairOut - 1) / kPairOut;
-    const int seg = strip_seg(G, ns, 4);
+    const int seg = adjoint_pair_rows(G);
     const long waves = (long)ns * ((G.ny + seg - 1) / seg);
     hipLaunchKernelGGL((k_adj2d_strip<T, TA>), dim3((waves + kPairWaves - 1) / kPairWaves),
                        dim3(64 * kPairWaves), 0, st, (const T *)un, (const TA *)lam2, (TA *)lam0,
@@ -390,6 +390,8 @@ bool adjoint_pairs(const Geo &G, bool f32, bool a32)
     return bytes < (1L << 31) && slots < (1L << 31);
 }
 
+int adjoint_pair_rows(const Geo &G) { return strip_seg(G, (G.nx + kPairOut - 1) / kPairOut, 4); }
+
 hipError_t launch_adjoint_pair(bool f32, bool a32, const void *un, const void *lam2, void *lam0,
                                double *partials, const Geo &G, const Phys &P, hipStream_t st)
 {
@@ -404,10 +406,19 @@ hipError_t launch_adjoint_pair(bool f32, bool a32, const void *un, const void *l
 // 2.9, 4.1 / 5.6, 4.7 / 6.6, 4.9 / 6.6, 7.4 / 10.6, 10.0 / 14.7 (what changes is how many
 // tiles fall on a compute unit); in strips 5.5 / 6.7, 5.9 / 6.8, 6.1 / 7.3, 6.0 / 7.8, 6.4
 // / 8.6, 7.8 / 10.9.
-int adjoint_levels_steps(const Geo &G)
+// Tiles grow with the grid: 16^2 keeps 6000 nodes on 100 compute units, 32^2 loses least
+// to halos (fastest of seven shapes at each size).
+int adjoint_levels_plan(const Geo &G, int *K)
 {
     const long nodes = (long)G.nx * G.ny;
-    return nodes > 140000 ? 0 : nodes > 50000 && nodes <= 75000 ? 3 : 5;
+    if (nodes > 140000) return -1;
+    *K = nodes > 50000 && nodes <= 75000 ? 3 : 5;
+    return nodes <= 12000 ? 0 : nodes <= 100000 ? 1 : 2;
+}
+void adjoint_levels_dims(int shape, int *cols, int *rows)
+{
+    *cols = shape == 0 ? 16 : 32;
+    *rows = shape < 2 ? 16 : 32;
 }
 
 template <typename T, typename TA, int TX, int TY, int R>
@@ -424,32 +435,34 @@ static hipError_t levels_launch(const void *first, const void *next, long stride
     return hipGetLastError();
 }
 
-// Tiles grow with the grid: 16^2 keeps 6000 nodes on 100 compute units, 32^2 loses least
-// to halos (fastest of seven shapes at each size).
 template <typename T, typename TA>
-static hipError_t levels_any(const void *first, const void *next, long stride, const void *lamK,
-                             void *lam0, double *partials, const Geo &G, const Phys &P, int K,
-                             hipStream_t st)
+static hipError_t levels_any(int shape, const void *first, const void *next, long stride,
+                             const void *lamK, void *lam0, double *partials, const Geo &G,
+                             const Phys &P, int K, hipStream_t st)
 {
-    const long nodes = (long)G.nx * G.ny;
-    if (nodes <= 12000)
+    switch (shape) {
+    case 0:
         return levels_launch<T, TA, 16, 16, 1>(first, next, stride, lamK, lam0, partials, G, P, K,
                                                st);
-    if (nodes <= 100000)
+    case 1:
         return levels_launch<T, TA, 32, 16, 1>(first, next, stride, lamK, lam0, partials, G, P, K,
                                                st);
-    return levels_launch<T, TA, 32, 16, 2>(first, next, stride, lamK, lam0, partials, G, P, K, st);
+    case 2:
+        return levels_launch<T, TA, 32, 16, 2>(first, next, stride, lamK, lam0, partials, G, P, K,
+                                               st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
-hipError_t launch_adjoint_levels(bool f32, bool a32, const void *first, const void *next,
-                                 long stride, const void *lamK, void *lam0, double *partials,
-                                 const Geo &G, const Phys &P, int K, hipStream_t st)
+hipError_t launch_adjoint_levels(bool f32, bool a32, int shape, const void *first,
+                                 const void *next, long stride, const void *lamK, void *lam0,
+                                 double *partials, const Geo &G, const Phys &P, int K,
+                                 hipStream_t st)
 {
-    if (f32 && a32)
-        return levels_any<float, float>(first, next, stride, lamK, lam0, partials, G, P, K, st);
-    if (f32)
-        return levels_any<float, double>(first, next, stride, lamK, lam0, partials, G, P, K, st);
-    return levels_any<double, double>(first, next, stride, lamK, lam0, partials, G, P, K, st);
+    const auto run = f32 && a32 ? levels_any<float, float>
+                     : f32      ? levels_any<float, double>
+                                : levels_any<double, double>;
+    return run(shape, first, next, stride, lamK, lam0, partials, G, P, K, st);
 }
 
 // ---- every level stored, larger grids ----------------------------------------------------
@@ -541,7 +554,7 @@ static hipError_t levels_strip(const void *src, void *dst, long stride, const Ge
                                const Phys &P, hipStream_t st)
 {
     const int ns = (G.nx + kLevelOut - 1) / kLevelOut;
-    const int seg = strip_seg(G, ns, 2 * K);
+    const int seg = levels_strip_rows(G, K);
     const long waves = (long)ns * ((G.ny + seg - 1) / seg);
     hipLaunchKernelGGL((k_levels_strip<T, K>), dim3((waves + kPairWaves - 1) / kPairWaves),
                        dim3(64 * kPairWaves), 0, st, (const T *)src, (T *)dst, stride, G, P, ns,
@@ -556,6 +569,10 @@ int levels_strip_steps(const Geo &G, bool f32)
 {
     if (12L * G.ps * (f32 ? 4 : 8) >= (1L << 31)) return 0;
     return f32 && (long)G.nx * G.ny < 2000000 ? 2 : kLevelStripMost;
+}
+int levels_strip_rows(const Geo &G, int K)
+{
+    return strip_seg(G, (G.nx + kLevelOut - 1) / kLevelOut, 2 * K);
 }
 hipError_t launch_levels_strip(bool f32, const void *src, void *dst, long stride, const Geo &G,
                                const Phys &P, int K, hipStream_t st)

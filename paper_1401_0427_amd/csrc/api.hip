@@ -492,24 +492,48 @@ static hipError_t step_once(lbm_ctx *c, const void *src, void *dst, hipStream_t 
     return launch_step(c->dim, c->f32, src, dst, c->G, c->P, c->L, st);
 }
 
-// k steps (1 <= k <= step_depth(c)) in one launch: level n in src, level n+k in dst.
-static hipError_t step_k(lbm_ctx *c, int k, const void *src, void *dst, hipStream_t st)
+// The launch of k steps (1 <= k <= step_depth(c)).
+static lbm_launch step_launch(const lbm_ctx *c, int k)
 {
-    if (k == 1) return step_once(c, src, dst, st);
-    if (c->tile >= 0)
-        return c->rest ? launch_tile2d_rest(c->f32, c->tile, src, dst, c->G, c->M, k, st)
-                       : launch_tile2d(c->f32, c->tile, src, dst, c->G, c->P, k, st);
-    if (c->rest)
-        return c->dim == 1
-                   ? launch_line_rest(c->f32, src, dst, c->G, c->M, k, st)
-                   : launch_step_rest2k(c->f32, src, dst, c->G, c->M, k, c->rest_seg_k[k], st);
-    if (c->dim == 2) {
-        if (c->x2 && k == 2)
-            return launch_step2x(c->f32, src, dst, c->G, c->P, kFuseSeg, st);
-        const int seg = c->xk_seg_k[k] > 0 ? c->xk_seg_k[k] : c->xk_seg > 0 ? c->xk_seg : kXkSeg;
-        return launch_step2k(c->f32, src, dst, c->G, c->P, k, seg, st);
+    lbm_launch l = {LBM_K_STEP, k, 0, 0};
+    if (k == 1) return l;
+    if (c->tile >= 0) {
+        l.kernel = LBM_K_TILE;
+        tile2d_dims(c->tile, &l.cols, &l.rows);
+    } else if (c->dim == 1) {
+        l.kernel = LBM_K_LINE;
+        l.cols = line_tile(c->G, c->rest, c->f32, k);
+        l.rows = 1;
+    } else if (c->x2 && k == 2) {
+        l.kernel = LBM_K_LDS2;
+        l.rows = kFuseSeg;
+    } else {
+        l.kernel = LBM_K_STRIP;
+        l.rows = c->rest              ? c->rest_seg_k[k]
+                 : c->xk_seg_k[k] > 0 ? c->xk_seg_k[k]
+                 : c->xk_seg > 0      ? c->xk_seg
+                                      : kXkSeg;
     }
-    return launch_line(c->f32, src, dst, c->G, c->P, k, st);
+    return l;
+}
+
+// That launch: level n in src, level n + l.steps in dst.
+static hipError_t step_k(lbm_ctx *c, const lbm_launch &l, const void *src, void *dst,
+                         hipStream_t st)
+{
+    switch (l.kernel) {
+    case LBM_K_TILE:
+        return c->rest ? launch_tile2d_rest(c->f32, c->tile, src, dst, c->G, c->M, l.steps, st)
+                       : launch_tile2d(c->f32, c->tile, src, dst, c->G, c->P, l.steps, st);
+    case LBM_K_LINE:
+        return c->rest ? launch_line_rest(c->f32, src, dst, c->G, c->M, l.steps, st)
+                       : launch_line(c->f32, src, dst, c->G, c->P, l.steps, st);
+    case LBM_K_LDS2: return launch_step2x(c->f32, src, dst, c->G, c->P, l.rows, st);
+    case LBM_K_STRIP:
+        return c->rest ? launch_step_rest2k(c->f32, src, dst, c->G, c->M, l.steps, l.rows, st)
+                       : launch_step2k(c->f32, src, dst, c->G, c->P, l.steps, l.rows, st);
+    default: return step_once(c, src, dst, st);
+    }
 }
 
 static int check_ctx(lbm_ctx *c)
@@ -546,7 +570,7 @@ static int ensure_chunk(lbm_ctx *c, int from)
     // chunk_len / fuse launches of fuse steps each; an even number of them, so
     // the chunk ends on the buffer it started from
     for (int k = 0; k < c->chunk_len / c->fuse && le == hipSuccess; ++k) {
-        le = step_k(c, c->fuse, c->buf[cur], c->buf[cur ^ 1], c->cap);
+        le = step_k(c, step_launch(c, c->fuse), c->buf[cur], c->buf[cur ^ 1], c->cap);
         cur ^= 1;
     }
     hipError_t ee = hipStreamEndCapture(c->cap, &g);
@@ -642,7 +666,7 @@ extern "C" int lbm_step(lbm_ctx *c, long nsteps)
             return LBM_OK;
         },
         [&](int k) -> int {
-            HIP_TRY(step_k(c, k, c->buf[c->cur], c->buf[c->cur ^ 1], c->st));
+            HIP_TRY(step_k(c, step_launch(c, k), c->buf[c->cur], c->buf[c->cur ^ 1], c->st));
             c->cur ^= 1;
             c->steps += k;
             return LBM_OK;
@@ -799,78 +823,142 @@ extern "C" int lbm_adjoint_step(lbm_ctx *c, const void *f_n, const void *lam_np1
     return LBM_OK;
 }
 
-// Steps of an adjoint sweep on an all-periodic 2D grid run several per launch: up to
-// adjoint_levels_steps (an odd number) over stored levels on small grids, two from every
-// second level on larger ones.  A sweep must end in the same one of its two buffers as
-// with one launch per step: odd launches keep that by themselves, pairs in even numbers.
+// Steps of an adjoint sweep on an all-periodic 2D grid run several per launch: an odd
+// number over stored levels on small grids (adjoint_levels_plan), two from every second
+// level on larger ones.  A sweep must end in the same one of its two buffers as with one
+// launch per step: odd launches keep that by themselves, pairs in even numbers.
 static bool multi_adjoint(const lbm_ctx *c)
 {
     return c->dim == 2 && c->G.bc[0] == BC_PERIODIC && c->G.bc[2] == BC_PERIODIC;
 }
-// Of nsteps steps, the first this many (levels n0 ..) run in pairs.
-static int paired_steps(const lbm_ctx *c, int nsteps)
+
+// The launches of nsteps adjoint steps, in order: launch(i, l, shape) for the steps n0 + i
+// .. n0 + i + l.steps - 1 (shape: of tiles).  Stops at the first non-zero return.
+template <typename F>
+static int walk_sweep(const lbm_ctx *c, int nsteps, F &&launch)
 {
-    const bool pairs = multi_adjoint(c) && adjoint_levels_steps(c->G) == 0 &&
-                       adjoint_pairs(c->G, c->f32, c->a32);
-    return pairs ? nsteps / 4 * 4 : 0;
+    int most = 0, shape = -1;
+    if (multi_adjoint(c)) shape = adjoint_levels_plan(c->G, &most);
+    const bool pairs = multi_adjoint(c) && shape < 0 && adjoint_pairs(c->G, c->f32, c->a32);
+    const int paired = pairs ? nsteps / 4 * 4 : 0;  // the first this many run in pairs
+    for (int i = nsteps; i > 0;) {
+        lbm_launch l = {LBM_K_STEP, 1, 0, 0};
+        if (i <= paired) {
+            l = {LBM_K_STRIP, 2, 0, adjoint_pair_rows(c->G)};
+        } else if (shape >= 0 && most > 1 && i > 2) {
+            l = {LBM_K_TILE, i < most ? (i - 1) | 1 : most, 0, 0};
+            adjoint_levels_dims(shape, &l.cols, &l.rows);
+        }
+        i -= l.steps;
+        const int rc = launch(i, l, shape);
+        if (rc) return rc;
+    }
+    return LBM_OK;
 }
 
 // nsteps adjoint steps from lam^{n0 + nsteps} in lam_a down to lam^{n0}, level
-// n0 + i of the forward state at level(i) (consecutive buffers from i = 1 on); *lam_out = 0 when lam^{n0} ends in lam_a, 1 when
-// in lam_b.
+// n0 + i of the forward state at level(i) (consecutive buffers from i = 1 on); *lam_out = 0
+// when lam^{n0} ends in lam_a, 1 when in lam_b.
 template <typename Level>
 static int adjoint_sweep(lbm_ctx *c, Level &&level, int nsteps, void *lam_a, void *lam_b,
                          double *dLds_partials, int *lam_out)
 {
-    const int paired = paired_steps(c, nsteps);
-    const int most = multi_adjoint(c) ? adjoint_levels_steps(c->G) : 0;
     const long stride = (long)(c->bytes / (c->f32 ? 4 : 8));
     void *hi = lam_a, *lo = lam_b;
-    for (int i = nsteps; i > 0;) {
-        if (i <= paired) {
-            i -= 2;
+    const int rc = walk_sweep(c, nsteps, [&](int i, const lbm_launch &l, int shape) -> int {
+        if (l.kernel == LBM_K_STRIP)
             HIP_TRY(launch_adjoint_pair(c->f32, c->a32, level(i), hi, lo, dLds_partials, c->G,
                                         c->P, c->st));
-        } else if (most > 1 && i > 2) {
-            const int k = i < most ? (i - 1) | 1 : most;
-            i -= k;
-            HIP_TRY(launch_adjoint_levels(c->f32, c->a32, level(i), level(i + 1), stride, hi, lo,
-                                          dLds_partials, c->G, c->P, k, c->st));
-        } else {
-            --i;
+        else if (l.kernel == LBM_K_TILE)
+            HIP_TRY(launch_adjoint_levels(c->f32, c->a32, shape, level(i), level(i + 1), stride, hi,
+                                          lo, dLds_partials, c->G, c->P, l.steps, c->st));
+        else
             HIP_TRY(launch_adjoint(c->dim, c->f32, c->a32, level(i), hi, lo, dLds_partials,
                                    c->d_adj_side, c->G, c->P, c->st));
-        }
         void *t = hi;
         hi = lo;
         lo = t;
+        return LBM_OK;
+    });
+    if (rc) return rc;
+    if (lam_out) *lam_out = hi == lam_a ? 0 : 1;
+    return LBM_OK;
+}
+
+// The launches that store every level of nsteps steps, in order: launch(i, l, shape) from
+// level i on (shape: of tiles).  Stops at the first non-zero return.
+template <typename F>
+static int walk_levels(const lbm_ctx *c, int nsteps, F &&launch)
+{
+    int most = 1;
+    const int shape = c->dim == 2 && !c->rest ? tile2d_levels_plan(c->G, &most) : -1;
+    if (shape < 0 && !c->rest && multi_adjoint(c)) most = levels_strip_steps(c->G, c->f32);
+    for (int i = 0; i < nsteps;) {
+        const int left = nsteps - i, launches = most > 1 ? (left + most - 1) / most : left;
+        lbm_launch l = {LBM_K_STEP, (left + launches - 1) / launches, 0, 0};
+        if (l.steps > 1 && shape >= 0) {
+            l.kernel = LBM_K_TILE;
+            tile2d_dims(shape, &l.cols, &l.rows);
+        } else if (l.steps > 1) {
+            l.kernel = LBM_K_STRIP;
+            l.rows = levels_strip_rows(c->G, l.steps);
+        }
+        const int rc = launch(i, l, shape);
+        if (rc) return rc;
+        i += l.steps;
     }
-    *lam_out = hi == lam_a ? 0 : 1;
     return LBM_OK;
 }
 
 // Every level of nsteps steps from `from`, level i into slot i - 1 of levels.
 static int store_levels(lbm_ctx *c, const void *from, int nsteps, void *levels)
 {
-    const int tile = c->dim == 2 && !c->rest ? tile2d_levels_steps(c->G) : 0;
-    const int strip = !c->rest && multi_adjoint(c) ? levels_strip_steps(c->G, c->f32) : 0;
-    const int most = tile ? tile : strip;
     const long stride = (long)(c->bytes / (c->f32 ? 4 : 8));
-    const void *prev = from;
-    for (int i = 0; i < nsteps;) {
+    return walk_levels(c, nsteps, [&](int i, const lbm_launch &l, int shape) -> int {
         void *dst = (char *)levels + (size_t)i * c->bytes;
-        const int left = nsteps - i, launches = most > 1 ? (left + most - 1) / most : left;
-        const int k = (left + launches - 1) / launches;
-        if (k > 1 && tile)
-            HIP_TRY(launch_tile2d_levels(c->f32, prev, dst, stride, c->G, c->P, k, c->st));
-        else if (k > 1)
-            HIP_TRY(launch_levels_strip(c->f32, prev, dst, stride, c->G, c->P, k, c->st));
+        const void *prev = i == 0 ? from : (char *)dst - c->bytes;
+        if (l.kernel == LBM_K_TILE)
+            HIP_TRY(launch_tile2d_levels(c->f32, shape, prev, dst, stride, c->G, c->P, l.steps,
+                                         c->st));
+        else if (l.kernel == LBM_K_STRIP)
+            HIP_TRY(launch_levels_strip(c->f32, prev, dst, stride, c->G, c->P, l.steps, c->st));
         else
             HIP_TRY(step_once(c, prev, dst, c->st));
-        i += k;
-        prev = (char *)levels + (size_t)(i - 1) * c->bytes;
-    }
-    return LBM_OK;
+        return LBM_OK;
+    });
+}
+
+extern "C" int lbm_run_plan(lbm_ctx *c, int run, long nsteps, lbm_launch *launches, int cap,
+                            long *n_launches)
+{
+    int rc = check_ctx(c);
+    if (rc) return rc;
+    if (run < LBM_RUN_STEP || run > LBM_RUN_ADJOINT)
+        return fail(LBM_EINVAL, "run must be one of LBM_RUN_* (got %d)", run);
+    if (run == LBM_RUN_ADJOINT && c->rest)
+        return fail(LBM_EINVAL, "the adjoint exists for D1Q2x2 and D2Q4x3");
+    if (nsteps < 0 || (run != LBM_RUN_STEP && nsteps > 0x7fffffffL))
+        return fail(LBM_EINVAL, "nsteps must be >= 0");
+    if (cap < 0 || (cap > 0 && !launches))
+        return fail(LBM_EINVAL, "launches must hold cap >= 0 entries");
+    long n = 0;
+    const auto put = [&](const lbm_launch &l) -> int {
+        if (n < cap) launches[n] = l;
+        ++n;
+        return LBM_OK;
+    };
+    const auto put_from = [&](int, const lbm_launch &l, int) { return put(l); };
+    if (run == LBM_RUN_STEP)
+        rc = walk_plan(
+            c, step_depth(c), c->merge > 0, 0, nsteps, [&]() -> int { return LBM_OK; },
+            [&](int k) -> int { return put(step_launch(c, k)); },
+            [&](long) -> int { return LBM_OK; });
+    else if (run == LBM_RUN_LEVELS)
+        rc = walk_levels(c, (int)nsteps, put_from);
+    else
+        rc = walk_sweep(c, (int)nsteps, put_from);
+    if (n_launches) *n_launches = n;
+    return rc;
 }
 
 extern "C" int lbm_adjoint_segment(lbm_ctx *c, const void *ck, int nsteps, void *work,

@@ -356,12 +356,23 @@ static void whole_launch(const void *src, void *dst, const Geo &G, const PH &P, 
                        (T *)dst, G, P, K);
 }
 
+// Whether a K-step launch takes the whole domain in one workgroup.
+static bool line_one_group(const Geo &G, int K)
+{
+    return step1k_whole(G) && (G.nx <= kLineWholeNodes || K > kLineMaxK);
+}
+int line_tile(const Geo &G, bool rest, bool f32, int K)
+{
+    if (line_one_group(G, K)) return G.nx;
+    return 64 * line_shape(G.nx, G.bc[0] == BC_PERIODIC, rest, f32, K, nullptr);
+}
+
 template <typename T, typename PH>
 static hipError_t line_launch(const void *src, void *dst, const Geo &G, const PH &P, int K,
                               hipStream_t st)
 {
     if (K < 1) return hipErrorInvalidValue;
-    if (step1k_whole(G) && (G.nx <= kLineWholeNodes || K > kLineMaxK)) {
+    if (line_one_group(G, K)) {
         if (G.nx <= 64)
             whole_launch<T, 1, 1>(src, dst, G, P, K, st);
         else if (G.nx <= 128)

@@ -58,15 +58,22 @@ hipError_t launch_levels_strip(bool f32, const void *src, void *dst, long stride
                                const Phys &P, int K, hipStream_t st);
 // Small 2D grids: K steps in one launch that stores every level (level k + 1 at dst + k *
 // stride elements; any faces), and K adjoint steps over stored levels (all-periodic;
-// level 0 at first, level j > 0 at next + (j - 1) * stride).  *_steps: K of the grid, 0
-// where single steps (two-step launches) are faster.
-int tile2d_levels_steps(const Geo &G);
-hipError_t launch_tile2d_levels(bool f32, const void *src, void *dst, long stride, const Geo &G,
-                                const Phys &P, int K, hipStream_t st);
-int adjoint_levels_steps(const Geo &G);
-hipError_t launch_adjoint_levels(bool f32, bool a32, const void *first, const void *next,
-                                 long stride, const void *lamK, void *lam0, double *partials,
-                                 const Geo &G, const Phys &P, int K, hipStream_t st);
+// level 0 at first, level j > 0 at next + (j - 1) * stride).  *_plan: the tile shape and
+// the K of the grid, -1 where strips or single steps are faster.
+int tile2d_levels_plan(const Geo &G, int *K);
+hipError_t launch_tile2d_levels(bool f32, int shape, const void *src, void *dst, long stride,
+                                const Geo &G, const Phys &P, int K, hipStream_t st);
+int adjoint_levels_plan(const Geo &G, int *K);
+hipError_t launch_adjoint_levels(bool f32, bool a32, int shape, const void *first,
+                                 const void *next, long stride, const void *lamK, void *lam0,
+                                 double *partials, const Geo &G, const Phys &P, int K,
+                                 hipStream_t st);
+// What a launch consists of: nodes of a tile, rows of a strip's segment.
+void tile2d_dims(int shape, int *cols, int *rows);
+void adjoint_levels_dims(int shape, int *cols, int *rows);
+int adjoint_pair_rows(const Geo &G);
+int levels_strip_rows(const Geo &G, int K);
+int line_tile(const Geo &G, bool rest, bool f32, int K);
 
 // Deterministic sum of n doubles into *out, n large: two launches, through kLongSum
 // doubles of scratch (csrc/adjoint.hip).

@@ -400,33 +400,38 @@ static const struct {
 } kLevelShapes[] = {
     {12000, kTile16, 5}, {50000, kTile32x16, 5}, {120000, kTile32x16, 4}, {700000, kTile64x32, 4}};
 
-int tile2d_levels_steps(const Geo &G)
+int tile2d_levels_plan(const Geo &G, int *K)
 {
     for (const auto &s : kLevelShapes)
-        if ((long)G.nx * G.ny <= s.nodes) return s.K;
-    return 0;
+        if ((long)G.nx * G.ny <= s.nodes) {
+            *K = s.K;
+            return s.shape;
+        }
+    return -1;
 }
 
 template <typename T>
-static hipError_t levels_any(const void *src, void *dst, long stride, const Geo &G, const Phys &P,
-                             int K, hipStream_t st)
+static hipError_t levels_any(int shape, const void *src, void *dst, long stride, const Geo &G,
+                             const Phys &P, int K, hipStream_t st)
 {
-    for (const auto &s : kLevelShapes) {
-        if ((long)G.nx * G.ny > s.nodes) continue;
-        switch (s.shape) {
-        case kTile16: return tile_launch<T, Phys, true, 16, 16, 1>(src, dst, stride, G, P, K, st);
-        case kTile32x16:
-            return tile_launch<T, Phys, true, 32, 16, 1>(src, dst, stride, G, P, K, st);
-        default: return tile_launch<T, Phys, true, 64, 8, 4>(src, dst, stride, G, P, K, st);
-        }
+    switch (shape) {
+    case kTile16: return tile_launch<T, Phys, true, 16, 16, 1>(src, dst, stride, G, P, K, st);
+    case kTile32x16: return tile_launch<T, Phys, true, 32, 16, 1>(src, dst, stride, G, P, K, st);
+    case kTile64x32: return tile_launch<T, Phys, true, 64, 8, 4>(src, dst, stride, G, P, K, st);
+    default: return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
-hipError_t launch_tile2d_levels(bool f32, const void *src, void *dst, long stride, const Geo &G,
-                                const Phys &P, int K, hipStream_t st)
+hipError_t launch_tile2d_levels(bool f32, int shape, const void *src, void *dst, long stride,
+                                const Geo &G, const Phys &P, int K, hipStream_t st)
 {
-    return f32 ? levels_any<float>(src, dst, stride, G, P, K, st)
-               : levels_any<double>(src, dst, stride, G, P, K, st);
+    return f32 ? levels_any<float>(shape, src, dst, stride, G, P, K, st)
+               : levels_any<double>(shape, src, dst, stride, G, P, K, st);
+}
+
+void tile2d_dims(int shape, int *cols, int *rows)
+{
+    *cols = kTileShapes[shape].tx;
+    *rows = kTileShapes[shape].ty * kTileShapes[shape].R;
 }
 
 } // namespace lbm

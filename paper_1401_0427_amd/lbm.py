@@ -78,9 +78,17 @@ class LbmBatchTuning(ctypes.Structure):
                 ("direct", ctypes.c_int)]
 
 
+class LbmLaunch(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int), ("steps", ctypes.c_int), ("cols", ctypes.c_int),
+                ("rows", ctypes.c_int)]
+
+
+RUNS = {"step": 0, "levels": 1, "adjoint": 2}
+KERNELS = {1: "step", 2: "lds2", 3: "strip", 4: "tile", 5: "line"}
+
 EXPORTS = [
     "lbm_layout", "lbm_init", "lbm_step", "lbm_step_buffers", "lbm_current",
-    "lbm_launch_info", "lbm_launch_plan", "lbm_export", "lbm_adjoint_segment",
+    "lbm_launch_info", "lbm_launch_plan", "lbm_run_plan", "lbm_export", "lbm_adjoint_segment",
     "lbm_step_levels", "lbm_adjoint_levels",
     "lbm_import", "lbm_moments", "lbm_moments_noalloc", "lbm_entropy", "lbm_adjoint_step", "lbm_adjoint_partials",
     "lbm_adjoint_terminal", "lbm_adjoint_grad_w0", "lbm_sum", "lbm_destroy",
@@ -115,6 +123,8 @@ def load(path: str = LIB_PATH):
                                  ctypes.POINTER(ctypes.c_long)]),
         "lbm_launch_plan": (ip, [vp, lp, ctypes.POINTER(ctypes.c_int), ip,
                                  ctypes.POINTER(ctypes.c_long)]),
+        "lbm_run_plan": (ip, [vp, ip, lp, ctypes.POINTER(LbmLaunch), ip,
+                              ctypes.POINTER(ctypes.c_long)]),
         "lbm_export": (ip, [vp, vp]),
         "lbm_step_levels": (ip, [vp, vp, ip, vp]),
         "lbm_adjoint_levels": (ip, [vp, vp, ip, vp, vp, vp, ctypes.POINTER(ctypes.c_int)]),
@@ -296,15 +306,30 @@ class Solver:
         return buf, steps.value
 
     def launch_info(self):
-        """dict(steps_per_launch, segment_rows, resident_blocks) chosen at init."""
+        """dict(steps_per_launch, segment_rows, resident_blocks) of the plan chosen at
+        init (a default plan is regrouped when it runs: run_plan)."""
         k, seg, res = ctypes.c_int(), ctypes.c_int(), ctypes.c_long()
         check(load().lbm_launch_info(self.ctx, ctypes.byref(k), ctypes.byref(seg),
                                      ctypes.byref(res)), "lbm_launch_info")
         return dict(steps_per_launch=k.value, segment_rows=seg.value,
                     resident_blocks=res.value)
 
+    def run_plan(self, nsteps, run="step"):
+        """The kernel launches of step(nsteps) ("step"), step_levels ("levels") or
+        adjoint_levels ("adjoint") of nsteps steps, as they run: a list of
+        dict(kernel, steps, cols, rows), kernel one of KERNELS."""
+        n = ctypes.c_long()
+        check(load().lbm_run_plan(self.ctx, RUNS[run], nsteps, None, 0, ctypes.byref(n)),
+              "lbm_run_plan")
+        ls = (LbmLaunch * max(n.value, 1))()
+        check(load().lbm_run_plan(self.ctx, RUNS[run], nsteps, ls, n.value, ctypes.byref(n)),
+              "lbm_run_plan")
+        return [dict(kernel=KERNELS[l.kernel], steps=l.steps, cols=l.cols, rows=l.rows)
+                for l in ls[:n.value]]
+
     def launch_plan(self, nsteps):
-        """Steps of each launch that step(nsteps) issues from the current step count."""
+        """The steps of each launch of step(nsteps) as planned from the current step
+        count; a default plan is regrouped when it runs (run_plan)."""
         n = ctypes.c_long()
         check(load().lbm_launch_plan(self.ctx, nsteps, None, 0, ctypes.byref(n)),
               "lbm_launch_plan")
