@@ -153,7 +153,7 @@ struct lbm_ctx {
     // Default plans (lbm_params.fuse_steps = 0): lbm_step regroups the plan's steps
     // into kernels of at most this many; 0 = one kernel per launch of the plan.
     int merge;
-    int tile;  // shape of the regrouped 2D launches; -1: wave strips
+    int tile;  // shape of the regrouped 2D launches; < 0: none
     bool x2;   // 2D two-step launches take the LDS strip kernel (all-periodic grids)
     void *buf[2];
     int cur;
@@ -405,8 +405,8 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
         int k = 0;
         // tiles, or wave strips with their own depth and segments where these can run
         // (all-periodic grids for D2Q5Q4Q4; planes below 2 GiB) and are faster
-        const int deep = rest ? (c->f32 ? kDeepRest2dF32 : kDefaultFuseRest2d)
-                              : step2k_depth(c->G, c->f32, c->fuse);
+        int deep = rest ? (c->f32 ? kDeepRest2dF32 : kDefaultFuseRest2d)
+                        : step2k_depth(c->G, c->f32, c->fuse);
         long cols = 0;
         if ((size_t)c->ps * (c->f32 ? 4 : 8) < ((size_t)1 << 31))
             cols = !rest ? step2k_cols(c->G, c->f32, deep)
@@ -414,7 +414,8 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
         c->tile = tile2d_plan(c->G, rest, c->f32, cols, &k);
         if (c->tile >= 0) {
             c->merge = k;
-        } else {
+        } else if (c->tile == kRunStrips) {
+            if (k > 0) deep = k;
             c->merge = deep;
             for (int i = 2; i <= deep; ++i) {
                 const int sk = rest ? rest2k_rows(c->G, c->f32, i) : step2k_rows(c->G, c->f32, i);

@@ -35,8 +35,10 @@ int line_steps(const Geo &G, bool rest, bool f32);
 
 // 2D grids, K steps per launch of register tiles (csrc/tile2d.hip), any faces; bitwise
 // equal to K single steps.  tile2d_plan: the tile shape and the steps per launch for a
-// grid, or -1 where the wave-strip launches, whose whole strips cover strip_cols columns
-// (0: there are none), are faster.
+// grid; kRunStrips where the wave-strip launches, whose whole strips cover strip_cols
+// columns (0: there are none), are faster, *K then their depth (0: the grid's own);
+// kRunSteps where one step per launch is.
+constexpr int kRunStrips = -1, kRunSteps = -2;
 int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K);
 hipError_t launch_tile2d(bool f32, int shape, const void *src, void *dst, const Geo &G,
                          const Phys &P, int K, hipStream_t st);

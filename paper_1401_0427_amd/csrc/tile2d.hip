@@ -280,6 +280,47 @@ static double tile_cost(const Geo &G, bool rest, bool f32, bool bnd, const TileS
     return (4.2 + mem + K * (lat > issue ? lat : issue)) / K;
 }
 
+// Grids at most kShortSide nodes high (flat) or wide (narrow).  Tiles of the shapes below,
+// chosen for grids of their area, are mostly empty there: 200000 x 2 MRT with faces FP32
+// took 44.8 us a step in them, 15.6 in single steps; 20000 x 2 MRT periodic FP32 5.7, in
+// tiles of 32 x 16 3.3, in strips 2.5.  Narrow grids: tiles of 16 x 16 (4 x 50000 FP64 6.6 us,
+// single steps and strips, which fill few lanes, 38 and 20).  Flat ones: tiles of 32 x 16,
+// six steps per launch while four rows are enough and all tiles are resident, else four;
+// strips or single steps where they are cheaper.  The costs are fits to 14 flat grids of
+// 32000 to 3 M nodes x 8 kinds, the choice within 15 % of the fastest: a tile has its share
+// of a launch and its issue; a strip an iteration per row and level or its share of issue
+// and memory per node.  Few rows leave little to share a strip's start, so it runs few
+// steps: FP64 1000000 x 3 in 4, 5, 7, 9 steps 43.5, 43.2, 48.3, 54.7 us a step, FP32 in 2,
+// 4, 8 34.4, 26.2, 39.6.
+constexpr int kShortSide = 8;
+static int short_plan(const Geo &G, bool rest, bool f32, bool bnd, bool strips, int *K)
+{
+    if (G.ny > kShortSide) {
+        *K = 3;
+        return kTile16;
+    }
+    const double nodes = (double)G.nx * G.ny, ny = G.ny;
+    const bool six = G.ny <= 4 && (G.nx + 19) / 20 <= 256 * kTileShapes[kTile32x16].resident;
+    const double each =  // us per tile and step
+        (rest ? 2.6e-3 : f32 ? 1.7e-3 : 2.0e-3) * (bnd ? 1.12 : 1.0);
+    const double tile = six ? 0.9 + 0.8 * each * ((G.nx + 19) / 20) : 1.4 + each * ((G.nx + 23) / 24);
+    *K = six ? 6 : 4;
+    if (strips) {
+        const double lat = bnd ? 3.3 + 0.52 * ny : 1.8 + 0.34 * ny;
+        const double node = bnd    ? (f32 ? 6.5 + 20 / ny : 11 + 22 / ny)
+                            : rest ? (f32 ? 8.5 + 20 / ny : 10 + 19 / ny)
+                                   : (f32 ? 5 + 13 / ny : 8.5 + 17 / ny);
+        const double all = node * nodes * 1e-6;
+        if ((lat > all ? lat : all) < tile) {
+            *K = f32 ? (rest || G.ny < 4 ? 3 : 4) : (bnd || G.ny < 3 ? 4 : 5);
+            return kRunStrips;
+        }
+    } else if (rest && bnd) {
+        if ((f32 ? 4.2 + 23e-6 * nodes : 4.5 + 37e-6 * nodes) < tile) return kRunSteps;
+    }
+    return kTile32x16;
+}
+
 // Shape by the number of nodes (measured fastest, us per step FP64 a = 0 with inflow /
 // wall / Neumann faces against one step per launch, at 35 x 20, 70 x 40, 140 x 80,
 // 280 x 160, 560 x 320: 0.94 / 4.75, 1.03 / 4.2, 1.34 / 4.3, 2.1 / 5.6, 3.9 / 8.9; all
@@ -301,6 +342,8 @@ int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K)
     const bool bnd = G.bc[0] != BC_PERIODIC || G.bc[2] != BC_PERIODIC;
     const long nodes = (long)G.nx * G.ny;
     int shape, lo = 2, hi = 10;
+    if (nodes >= 5000 && (G.nx <= kShortSide || G.ny <= kShortSide))
+        return short_plan(G, rest, f32, bnd, strip_cols > 0, K);
     if (nodes < 5000) {
         shape = kTile16;
     } else if (nodes < (bnd || rest ? 30000 : 23500)) {
@@ -334,7 +377,10 @@ int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K)
         const long limit = rest ? (f32 ? 520000 : 270000)
                            : bnd ? (f32 ? 1500000 : 640000)
                                  : (f32 ? 450000 : 300000);
-        if ((double)covered > (double)limit * strip_cols / (1.1 * G.nx)) return -1;
+        if ((double)covered > (double)limit * strip_cols / (1.1 * G.nx)) {
+            *K = 0;
+            return kRunStrips;
+        }
     }
     return shape;
 }
