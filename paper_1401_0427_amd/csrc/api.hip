@@ -154,6 +154,8 @@ struct lbm_ctx {
     // into kernels of at most this many; 0 = one kernel per launch of the plan.
     int merge;
     int tile;  // shape of the regrouped 2D launches; < 0: none
+    int alone;   // of these: runs up to this long in one launch
+    bool apart;  // runs of two steps as single ones
     bool x2;   // 2D two-step launches take the LDS strip kernel (all-periodic grids)
     void *buf[2];
     int cur;
@@ -324,13 +326,13 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
             // device (rest2k_fills), else one step per launch
             int k = want ? (want > kMaxFuseRest2d ? kMaxFuseRest2d : want) : kDefaultFuseRest2d;
             long slots = 0;
-            const int seg = k >= 2 ? rest2k_seg(c->G, c->f32, k, &slots) : 0;
+            const int seg = k >= 2 ? rest2k_rows(c->G, c->f32, k, &slots) : 0;
             c->rest_seg = seg;
             if (k >= 2 && seg > 0 && (want || rest2k_fills(c->G, c->f32))) {
                 c->fuse = k;
                 c->rest_slots = slots;
                 for (int kk = 2; kk <= k; ++kk) {
-                    const int sk = kk == k ? seg : rest2k_seg(c->G, c->f32, kk, nullptr);
+                    const int sk = kk == k ? seg : rest2k_rows(c->G, c->f32, kk, nullptr);
                     c->rest_seg_k[kk] = sk > 0 ? sk : seg;
                 }
             } else {
@@ -400,13 +402,14 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
     c->st = (hipStream_t)p->stream;
     c->merge = 0;
     c->tile = -1;
+    c->alone = 0;
+    c->apart = false;
     if (p->fuse_steps == 0 && dim == 1) c->merge = line_steps(c->G, rest, c->f32);
     if (p->fuse_steps == 0 && dim == 2) {
         int k = 0;
         // tiles, or wave strips with their own depth and segments where these can run
         // (all-periodic grids for D2Q5Q4Q4; planes below 2 GiB) and are faster
-        int deep = rest ? (c->f32 ? kDeepRest2dF32 : kDefaultFuseRest2d)
-                        : step2k_depth(c->G, c->f32, c->fuse);
+        int deep = rest ? rest2k_depth(c->G, c->f32) : step2k_depth(c->G, c->f32, c->fuse);
         long cols = 0;
         if ((size_t)c->ps * (c->f32 ? 4 : 8) < ((size_t)1 << 31))
             cols = !rest ? step2k_cols(c->G, c->f32, deep)
@@ -414,11 +417,19 @@ extern "C" int lbm_init(const lbm_params *p, const double *h0, const double *qx0
         c->tile = tile2d_plan(c->G, rest, c->f32, cols, &k);
         if (c->tile >= 0) {
             c->merge = k;
+            // 200^2 FP64: two steps in one tile launch 8.5 us, MRT 9.3, two launches 8.1, 8.6
+            // (300^2 9.7, 13)
+            const long nodes = (long)p->nx * p->ny;
+            c->apart = !c->f32 && c->G.bc[0] == BC_PERIODIC && c->G.bc[2] == BC_PERIODIC &&
+                       nodes > 30000 && nodes < 50000;
         } else if (c->tile == kRunStrips) {
             if (k > 0) deep = k;
             c->merge = deep;
-            for (int i = 2; i <= deep; ++i) {
-                const int sk = rest ? rest2k_rows(c->G, c->f32, i) : step2k_rows(c->G, c->f32, i);
+            const bool allper = c->G.bc[0] == BC_PERIODIC && c->G.bc[2] == BC_PERIODIC;
+            if (!rest && !c->f32 && allper && k == 0) c->alone = kDeepStripF64;
+            for (int i = 2; i <= (deep > c->alone ? deep : c->alone); ++i) {
+                const int sk = rest ? rest2k_rows(c->G, c->f32, i, nullptr)
+                                    : step2k_rows(c->G, c->f32, i);
                 (rest ? c->rest_seg_k : c->xk_seg_k)[i] = sk > 0 ? sk : kXkMinSeg;
             }
         }
@@ -493,7 +504,7 @@ static hipError_t step_once(lbm_ctx *c, const void *src, void *dst, hipStream_t 
     return launch_step(c->dim, c->f32, src, dst, c->G, c->P, c->L, st);
 }
 
-// The launch of k steps (1 <= k <= step_depth(c)).
+// The launch of k steps (1 <= k <= step_depth(c) or c->alone).
 static lbm_launch step_launch(const lbm_ctx *c, int k)
 {
     lbm_launch l = {LBM_K_STEP, k, 0, 0};
@@ -505,7 +516,7 @@ static lbm_launch step_launch(const lbm_ctx *c, int k)
         l.kernel = LBM_K_LINE;
         l.cols = line_tile(c->G, c->rest, c->f32, k);
         l.rows = 1;
-    } else if (c->x2 && k == 2) {
+    } else if (c->x2 && k == 2 && c->merge == 0) {
         l.kernel = LBM_K_LDS2;
         l.rows = kFuseSeg;
     } else {
@@ -596,11 +607,25 @@ static int ensure_chunk(lbm_ctx *c, int from)
 // (the state is read and written once), so 20 steps run as 7 + 7 + 6 rather
 // than 8 + 8 + 4 (4096^2 FP64: 2.18 vs 2.29 ms).  A remainder of one step takes
 // the one-step kernel, the cheapest launch.  even: spread whatever the remainder
-// (regrouped kernels).
+// (regrouped kernels), except that
+//   - FP64 strips of kLoneStepNodes and more keep the one step (us as 7 + 1 and 4 + 4 steps
+//     with faces 4096^2 1338 and 1391, 1500^2 217 and 224, MRT as 5 + 1 and 3 + 3 1390 and
+//     1590; FP32 as 8 + 1 and 5 + 4 2048^2 266 and 198, MRT 4096^2 as 7 + 1 and 4 + 4 1107 and
+//     1022);
+//   - a run of up to c->alone steps takes one launch (1024^2 FP64 8 steps 95, 4 + 4 104);
+//   - two steps where c->apart run as single ones.
+static const long kLoneStepNodes = 2000000;
 static int next_launch_steps(const lbm_ctx *c, long F, bool even, long todo)
 {
     if (todo <= 1 || F <= 1) return (int)(todo < 1 ? todo : 1);
     const long r = todo % F;
+    if (even) {
+        if (todo <= c->alone) return (int)todo;
+        if (todo == 2 && c->apart) return 1;
+        if (r == 1 && c->tile == kRunStrips && !c->f32 &&
+            (long)c->G.nx * c->G.ny >= kLoneStepNodes)
+            return (int)(todo < F ? todo : F);
+    }
     if (!even && (c->dim != 2 || r <= 1)) return (int)(todo < F ? todo : F);
     const long launches = (todo + F - 1) / F;
     return (int)((todo + launches - 1) / launches);

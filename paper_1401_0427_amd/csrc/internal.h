@@ -185,6 +185,7 @@ int step2k_seg(const Geo &G, bool f32, int K, int min_seg, bool *full, long *slo
 // 4096^2 takes the 256-lane strips to two workgroups per compute unit, 62 against 56 us);
 // below 800 000 nodes 5 (680^2 4.75, 6 steps 4.9, 8 steps 5.5).  With faces FP64 7, FP32 5
 // below 2 M nodes (1300^2 12.7, 8 steps 14.5), else the plan's.
+constexpr int kDeepStripF64 = 9;  // the deepest of these
 int step2k_depth(const Geo &G, bool f32, int plan);
 long step2k_cols(const Geo &G, bool f32, int K);  // columns their whole strips cover
 int step2k_rows(const Geo &G, bool f32, int K);  // segment rows of those launches

@@ -183,23 +183,28 @@ __global__ void __launch_bounds__(256) k_step_rest1d(const T *__restrict__ src, 
 // each strip edge take values from outside the valid range and are not stored; the
 // first 2 (K - 1) iterations store nothing and skip the collisions of the levels
 // that have no row yet.
-//   A strip owns whole 64-byte pieces of a row (rest2k_out).  All planes share one
+//   A strip owns whole 64-byte (FP32: 16-byte) pieces of a row (rest2k_out).  All planes share one
 // buffer descriptor where they lie below 2 GiB together (else BIG: one per plane);
 // accesses that must not happen carry an offset the hardware drops, so the loop has
 // no branch and the loads of the next row stay in flight.  Bound by the issue of FP64
 // operations on small grids and by the state through memory from about 2048^2 on.  Two
 // wavefronts fit a SIMD up to K = 5 FP64 (230 registers) and 7 FP32; with 64-bit
 // addresses, permutes and a second row buffer it was one (268): 1024^2 FP64, K = 5, 14.6
-// us a step, 9.9 now, 4096^2 FP32 135, 114 at K = 7; 4096^2 FP64 160 either way (4.4 TB/s).
+// us a step, 9.9 now, 4096^2 FP32 135, 107 at K = 7; 4096^2 FP64 160 either way (4.4 TB/s).
+// FP64 K = 6 spills at two wavefronts and takes one (2048^2 48.3 us a step and 34.8).
+// Columns a strip owns: as many as the halo lanes leave, in whole pieces of a row.  FP32
+// pieces of 16 columns lose up to a fifth of the lanes (48 of 64 at every K from 2 to 7; in
+// fours 60, 60, 56, 56, 52, 52): us a step 7 steps 2048^2 32.5 and 30.1, 1024^2 11.5 and 10.3,
+// 100000 x 16 20.6 and 14.2.  FP64 ones of 8 cost less (56 or 48) than parts of lines.
 template <typename T, int K>
 constexpr int rest2k_out()
 {
-    constexpr int piece = 64 / (int)sizeof(T);
+    constexpr int piece = sizeof(T) == 4 ? 4 : 8;
     return (64 - 2 * (K - 1)) / piece * piece;
 }
 
 template <typename T, int K, bool BIG>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, sizeof(T) == 8 && K > 5 ? 1 : 2)
     k_step_rest2d_k(const T *__restrict__ src, T *__restrict__ dst, Geo G, Mrt M, int nstrips,
                     int seg)
 {
@@ -339,34 +344,9 @@ static int rest2k_per_cu(bool f32, int K, int *ncu)
     }
 }
 
-int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out)
+int rest2k_depth(const Geo &G, bool f32)
 {
-    int ncu = 0;
-    if (slots_out) *slots_out = 0;
-    const int per = rest2k_per_cu(f32, K, &ncu);
-    const long slots = (long)ncu * per;
-    if (slots_out) *slots_out = slots;
-    if (slots <= 0) return 0;
-    const int WO = rest2k_wo(f32, K);
-    const long ngroups = ((G.nx + WO - 1) / WO + 3) / 4;
-    // segment length of the fewest rows computed per wavefront over whole rounds of
-    // resident workgroups (halo rows: 2 (K - 1) per segment)
-    int best = 0;
-    double best_cost = 0.0;
-    for (int nseg = 1; nseg <= G.ny; ++nseg) {
-        const int sg = (G.ny + nseg - 1) / nseg;
-        if (sg < kRestMinSeg && nseg > 1) break;  // short grids: one segment
-        if ((G.ny + sg - 1) / sg != nseg) continue;
-        const long blocks = ngroups * nseg;
-        const long rounds = (blocks + slots - 1) / slots;
-        double cost = (double)rounds * (sg + 2 * (K - 1));
-        if (blocks < slots) cost *= (double)slots / (double)blocks;
-        if (best == 0 || cost < best_cost) {
-            best = sg;
-            best_cost = cost;
-        }
-    }
-    return best;
+    return f32 ? kDeepRest2dF32 : (long)G.nx * G.ny < 3000000 ? 5 : 6;
 }
 
 long rest2k_cols(const Geo &G, bool f32, int K)
@@ -379,24 +359,27 @@ bool rest2k_fills(const Geo &G, bool f32)
 {
     int ncu = 0;
     if (rest2k_per_cu(f32, 5, &ncu) <= 0) return false;
-    int nseg = 1;  // most segments of at least kRestMinSeg rows
+    int nseg = 1;  // most segments of at least 16 rows
     for (int n = 2; n <= G.ny; ++n) {
         const int sg = (G.ny + n - 1) / n;
-        if (sg < kRestMinSeg) break;
+        if (sg < 16) break;
         if ((G.ny + sg - 1) / sg == n) nseg = n;
     }
     return 3L * (((G.nx + 55) / 56 + 3) / 4) * nseg >= (f32 ? 2L : 1L) * ncu;
 }
 
-// Rows per segment for the regrouped launches of default plans: an iteration of two
+// Rows per segment: an iteration of two
 // workgroups on a compute unit takes 1.97 times that of one (4096^2 FP64, 5 steps: 4.95
 // and 2.47 us), so a second one only shortens the tail; the start of a segment costs 1.3
 // iterations per level.  1024^2 FP64, 5 steps: 49 segments of 21 rows (one workgroup
-// each) 9.9 us a step, 64 of 16 (two on some) 13.0.
-int rest2k_rows(const Geo &G, bool f32, int K)
+// each) 9.9 us a step, 64 of 16 (two on some) 13.0.  Choosing them by whole rounds of resident
+// workgroups instead: 4096^2 FP64, 5 steps, 849 us a launch, 770 so; 1024^2 FP32, 6 steps, 83,
+// 61.
+int rest2k_rows(const Geo &G, bool f32, int K, long *slots)
 {
     int ncu = 0;
-    const int per = std::min(rest2k_per_cu(f32, K, &ncu), 2);
+    const int resident = rest2k_per_cu(f32, K, &ncu), per = std::min(resident, 2);
+    if (slots) *slots = (long)ncu * resident;
     if (per <= 0) return 0;
     const int WO = rest2k_wo(f32, K);
     const long ngroups = ((G.nx + WO - 1) / WO + 3) / 4;

@@ -7,19 +7,18 @@ namespace lbm {
 
 // D2Q5Q4Q4 on all-periodic grids, K = 2 .. kMaxFuseRest2d steps per launch
 // (one wavefront per 64-column strip, four to a 256-thread workgroup, segments of
-// `seg` rows; bitwise equal to K single steps).  rest2k_seg: the segment length
-// for the device's resident workgroups (0 if it cannot be queried), slots_out the
-// resident workgroups; rest2k_fills: whether default plans take it, segments of 16 rows
-// giving a third of a workgroup (FP32: two thirds) per compute unit.
+// `seg` rows; bitwise equal to K single steps).  rest2k_rows: the segment length (0 if
+// the device cannot be queried), *slots (may be NULL) the resident workgroups; rest2k_fills:
+// whether default plans take it, segments of 16 rows giving a third of a workgroup (FP32: two
+// thirds) per compute unit.
 constexpr int kMaxFuseRest2d = 6;
-// Depth of the regrouped launches of default FP32 plans (us a step at 2048^2 and 4096^2
-// for 5, 6, 7, 8 steps: 33.3, 32.1, 32.5, 33.1 and 119, 117, 114, 113); FP64 keeps the
-// plan's 5 (1024^2: 9.9, 6 steps 12.9; 4096^2: 160, 156; from 6 on it spills registers).
+// Depth of the regrouped launches of default plans: FP32 7 (us a step at 2048^2 and 4096^2 for
+// 5, 6, 7 steps: 29.9, 30.0, 29.9 and 115, 107, 105); FP64 5, from 3 M nodes on 6 (one wavefront
+// per SIMD; 5 and 6 steps at 1024^2 9.5 and 10.4, 2048^2 39.4 and 34.8, 4096^2 154 and 135).
 constexpr int kDeepRest2dF32 = 7;
-int rest2k_rows(const Geo &G, bool f32, int K);  // segment rows of those launches
+int rest2k_depth(const Geo &G, bool f32);
+int rest2k_rows(const Geo &G, bool f32, int K, long *slots);
 long rest2k_cols(const Geo &G, bool f32, int K);  // columns their whole strips cover
-constexpr int kRestMinSeg = 16;
-int rest2k_seg(const Geo &G, bool f32, int K, long *slots_out);
 bool rest2k_fills(const Geo &G, bool f32);
 hipError_t launch_step_rest2k(bool f32, const void *src, void *dst, const Geo &G, const Mrt &M,
                               int K, int seg, hipStream_t st);
