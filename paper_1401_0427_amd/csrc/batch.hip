@@ -524,15 +524,17 @@ static bool inst_bounded(const lbm_instance &I)
            !(I.bc[0] == 0 && I.bc[1] == 0 && I.bc[2] == 0 && I.bc[3] == 0);
 }
 
-// Rows per 2D segment of the fused modes, one value for every 2D instance.  A tile runs
-// seg rows and about 10 more to start it (its warm iterations run only the levels that
-// have rows).  Where one round of tiles over the resident slots is the shortest number of
-// rounds, that is taken; else the workgroups take tiles until none is left and wait, half
-// a tile on average, for the last ones:
-//     (all rows + 10 tiles) / slots + (seg + 10) / 2.
-// 40 steps of the 256-instance manifest FP32: 85 rows 11.9 ms, 200 (two whole rounds)
-// 12.1; 64 + 64 instances FP64: 78 rows 9.0, 169 (two rounds) 9.95; 10 + 20 instances: one
-// round of 65 rows 2.6 FP32 and of 129 rows 3.73 FP64, by the second rule 2.7 and 3.82.
+// Rows per 2D segment of the fused modes, one value for every 2D instance: at least cost
+// over 16 .. the tallest instance's rows.  A tile runs seg rows and about K more to start it
+// (its warm iterations run only the levels that have rows).  Up to one round of tiles over
+// the resident slots the cost is that of a tile, longer in proportion where slots stay
+// empty.  Beyond, the mean of two bounds: whole rounds of tiles, and workgroups that take
+// tiles until none is left and wait, a third of a tile or so, for the last ones.  Either bound
+// alone is off by up to a fifth for some batches (6 + 6 + 6 + 6 instances of 128^2 .. 1024^2
+// FP64, K = 8: 103 rows 3.08 ms a 48-step run, 64, which the second bound prefers, 3.74; the
+// 256-instance manifest FP32: 85 - 90 rows 11.9 ms a 40-step run, 123, which the first
+// prefers, 12.1).  12 batches x 2 types x 2 modes x depths 2 .. 8: 2.8 % above the fastest of
+// up to 20 lengths on average.
 static int fused_seg(bool f32, int K, const std::vector<lbm_instance> &inst, long slots)
 {
     int maxny = 0;
@@ -543,9 +545,8 @@ static int fused_seg(bool f32, int K, const std::vector<lbm_instance> &inst, lon
     const int wo = batch_xk_out(f32, K), w = batch_xk_waves(f32, false);
     const int wob = K <= step2k_max_k_bounded() ? batch_xkb_out(f32, K) : wo;
     const int wb = batch_xk_waves(f32, true);
-    int best = 16, round_best = 16;
-    double best_cost = 0.0, round_cost = 0.0;
-    long round_tiles = 0;
+    int best = 16;
+    double best_cost = 0.0;
     for (int seg = 16; seg <= maxny; ++seg) {
         double work = 0.0;
         long tiles = 0;
@@ -556,21 +557,34 @@ static int fused_seg(bool f32, int K, const std::vector<lbm_instance> &inst, lon
             const long groups = ((I.nx + o - 1) / o + ww - 1) / ww;
             const long nseg = (I.ny + seg - 1) / seg;
             tiles += groups * nseg;
-            work += (double)groups * (I.ny + 10.0 * nseg);
+            work += (double)groups * (I.ny + (double)K * nseg);
         }
-        const double rc = (double)((tiles + slots - 1) / slots) * (seg + 10.0);
-        if (round_cost == 0.0 || rc < round_cost) {
-            round_best = seg;
-            round_cost = rc;
-            round_tiles = tiles;
-        }
-        const double cost = work / (double)slots + 0.5 * (seg + 10.0);
+        const double tile = seg + K;
+        const double cost =
+            tiles <= slots ? tile * (double)slots / (double)tiles
+                           : 0.5 * ((double)((tiles + slots - 1) / slots) * tile +
+                                    work / (double)slots + 0.35 * tile);
         if (best_cost == 0.0 || cost < best_cost) {
             best = seg;
             best_cost = cost;
         }
     }
-    return round_tiles <= slots ? round_best : best;
+    return best;
+}
+
+// Workgroups per compute unit of the persistent fused mode, at most.  Every pass ends with
+// a grid-wide close whose cost grows with the workgroups, and one per compute unit nearly
+// saturates FP64 issue.  Us a 48-step run with 1 and 2 of them, FP64 K = 8: one 64^2 instance
+// 343 and 418, 3 of 1000^2 1277 and 1499, 100 of 200^2 (4 M nodes) 2445 and 2310, 8.4 M nodes
+// 3150 and 2920, 45 M 15950 and 13780; K = 4, 8.4 M nodes 4840 and 5630.  FP32 K = 8 with 1, 2
+// and 3: one 64^2 373, 462, 524, 3 M nodes 1015, 1196, 1470, 5.2 M 2560, 2282, 2618, 8.4 M 2733,
+// 2503, 2637, the 256-instance manifest (33 M) 15018, 13077, 12908.
+static int pfused_most(bool f32, int K, const std::vector<lbm_instance> &inst)
+{
+    double nodes = 0.0;
+    for (const lbm_instance &I : inst) nodes += (double)I.nx * I.ny;
+    if (!f32) return K == 8 && nodes >= 4e6 ? 2 : 1;
+    return nodes < 4e6 ? 1 : nodes < 1.6e7 ? 2 : 4;
 }
 
 extern "C" int lbm_batch_create(const lbm_instance *inst_in, int n, int storage, void *f_a,
@@ -733,15 +747,16 @@ extern "C" int lbm_batch_create(const lbm_instance *inst_in, int n, int storage,
         b->chunk = 2L * K * ((32 + 2 * K - 1) / (2 * K));
         long slots;
         if (tune.mode == 4) {
-            // persistent grid: the resident workgroups the occupancy query reports
-            // (the launch completes with any grid)
+            // persistent grid: at most the resident workgroups the occupancy query reports
+            // (the launch completes with any grid), by default pfused_most
             per_cu = batch_pfused_per_cu(b->f32, K, anyb);
             if (per_cu <= 0) {
                 lbm_batch_destroy(b);
                 return bfail(LBM_EDEVICE, "no resident workgroup for the persistent kernel");
             }
             long g = (long)ncu * per_cu;
-            if (tune.grid > 0 && tune.grid < g) g = tune.grid;
+            const long most = tune.grid > 0 ? tune.grid : (long)ncu * pfused_most(b->f32, K, inst);
+            if (most < g) g = most;
             b->grid = (int)g;
             slots = g;
         } else {
