@@ -382,9 +382,12 @@ static hipError_t strip_launch(const void *un, const void *lam2, void *lam0, dou
 }
 
 // The strip kernel addresses whole buffers with 32-bit byte offsets, of which the upper
-// half marks dropped accesses.
+// half marks dropped accesses.  Flat grids below kPairNodes take single steps (20000 x 3 FP64
+// 4.9 us, in strips 6.5; 50000 x 2 8.3 and 5.4).
+constexpr long kPairNodes = 75000;
 bool adjoint_pairs(const Geo &G, bool f32, bool a32)
 {
+    if ((long)G.nx * G.ny < kPairNodes) return false;
     const long bytes = 12L * G.ps * (f32 && a32 ? 4 : 8);
     const long slots = adj_slots_row(G.nx) * (long)G.ny * 8;
     return bytes < (1L << 31) && slots < (1L << 31);
@@ -400,20 +403,37 @@ hipError_t launch_adjoint_pair(bool f32, bool a32, const void *un, const void *l
     return strip_launch<double, double>(un, lam2, lam0, partials, G, P, st);
 }
 
-// Steps per launch over stored levels, by nodes; 0: two-step launches from every second
-// level are faster.  Us a step FP32 / FP64 at 200^2, 256^2, 300^2, 350^2, 400^2, 512^2: 3
-// steps 2.7 / 3.2, 3.6 / 4.6, 5.0 / 7.1, 5.8 / 7.7, 6.4 / 8.6, 8.9 / 12.8; 5 steps 2.3 /
-// 2.9, 4.1 / 5.6, 4.7 / 6.6, 4.9 / 6.6, 7.4 / 10.6, 10.0 / 14.7 (what changes is how many
-// tiles fall on a compute unit); in strips 5.5 / 6.7, 5.9 / 6.8, 6.1 / 7.3, 6.0 / 7.8, 6.4
-// / 8.6, 7.8 / 10.9.
-// Tiles grow with the grid: 16^2 keeps 6000 nodes on 100 compute units, 32^2 loses least
-// to halos (fastest of seven shapes at each size).
+// Shape and steps per launch over stored levels: the smallest tiles and the most steps whose
+// tiles all run at once, one per compute unit (16^2 ones, which share it, in nodes), -1 where
+// none do: two-step launches from every second level are faster there, or single steps.  Us
+// a step FP32 / FP64 in tiles of 32 x 16 with 5 and 3 steps, 32 x 32 with 5, and strips: 200^2
+// (225 tiles of the first) 2.3 / 2.9, 2.6 / 3.1, 3.4 / 4.0, 5.4 / 6.6; 200 x 225 (261) 3.1 / 4.1,
+// 2.7 / 3.4, 3.5 / 4.0, 5.5 / 6.7; 256^2 4.0 / 5.1, 3.5 / 4.5, 3.7 / 4.6, 5.8 / 6.7; 128 x 512 (258
+// tiles of the second) 4.1 / 5.4, 4.5 / 5.6, 3.7 / 4.7, 5.8 / 6.7; 400^2 (289 of the third) 6.5 /
+// 10.2, 6.5 / 10.2, - / 9.5, 6.0 / 8.3.  Narrow grids fill few lanes of anything but 16^2 tiles
+// (3 x 100000 FP64 27 us a step, strips 77, single ones 130).
+static long levels_tiles(const Geo &G, int shape, int K)
+{
+    int tx, rows;
+    adjoint_levels_dims(shape, &tx, &rows);
+    const int wo = tx - 8, ho = rows - 2 * (K - 1);
+    return (long)((G.nx + wo - 1) / wo) * ((G.ny + ho - 1) / ho);
+}
 int adjoint_levels_plan(const Geo &G, int *K)
 {
     const long nodes = (long)G.nx * G.ny;
-    if (nodes > 140000) return -1;
-    *K = nodes > 50000 && nodes <= 75000 ? 3 : 5;
-    return nodes <= 12000 ? 0 : nodes <= 100000 ? 1 : 2;
+    *K = 5;
+    if (nodes <= 2000 || (nodes <= 12000 && G.ny > 8)) return 0;
+    if (G.nx <= 8) {
+        *K = 3;
+        return 0;
+    }
+    if (levels_tiles(G, 1, 5) <= 256) return 1;
+    if (levels_tiles(G, 1, 3) <= 256) {
+        *K = 3;
+        return 1;
+    }
+    return levels_tiles(G, 2, 5) <= 256 ? 2 : -1;
 }
 void adjoint_levels_dims(int shape, int *cols, int *rows)
 {
@@ -564,9 +584,11 @@ static hipError_t levels_strip(const void *src, void *dst, long stride, const Ge
 
 // Steps per launch (us a step for K = 2 / 3 / 4 at 1024^2 and 2048^2: FP32 16.8 / 18.0 /
 // 19.7 and 76 / 73 / 71, FP64 35.1 / 32.3 / 29.7 and 124 / 114 / 108); 0 where the
-// buffers are beyond 32-bit byte offsets.
+// buffers are beyond 32-bit byte offsets, and on flat grids, where a segment's start is not
+// made up for (1000000 x 3 FP32 64 us a step, single ones 53; 100000 x 16 33.8 and 28.7).
 int levels_strip_steps(const Geo &G, bool f32)
 {
+    if (G.ny <= (f32 ? 16 : 8)) return 0;
     if (12L * G.ps * (f32 ? 4 : 8) >= (1L << 31)) return 0;
     return f32 && (long)G.nx * G.ny < 2000000 ? 2 : kLevelStripMost;
 }

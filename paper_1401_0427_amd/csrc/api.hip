@@ -917,8 +917,9 @@ template <typename F>
 static int walk_levels(const lbm_ctx *c, int nsteps, F &&launch)
 {
     int most = 1;
-    const int shape = c->dim == 2 && !c->rest ? tile2d_levels_plan(c->G, &most) : -1;
-    if (shape < 0 && !c->rest && multi_adjoint(c)) most = levels_strip_steps(c->G, c->f32);
+    const int shape = c->dim == 2 && !c->rest ? tile2d_levels_plan(c->G, c->f32, &most) : -1;
+    if (shape < 0)
+        most = !c->rest && multi_adjoint(c) ? levels_strip_steps(c->G, c->f32) : 1;
     for (int i = 0; i < nsteps;) {
         const int left = nsteps - i, launches = most > 1 ? (left + most - 1) / most : left;
         lbm_launch l = {LBM_K_STEP, (left + launches - 1) / launches, 0, 0};

@@ -61,7 +61,7 @@ hipError_t launch_levels_strip(bool f32, const void *src, void *dst, long stride
 // stride elements; any faces), and K adjoint steps over stored levels (all-periodic;
 // level 0 at first, level j > 0 at next + (j - 1) * stride).  *_plan: the tile shape and
 // the K of the grid, -1 where strips or single steps are faster.
-int tile2d_levels_plan(const Geo &G, int *K);
+int tile2d_levels_plan(const Geo &G, bool f32, int *K);
 hipError_t launch_tile2d_levels(bool f32, int shape, const void *src, void *dst, long stride,
                                 const Geo &G, const Phys &P, int K, hipStream_t st);
 int adjoint_levels_plan(const Geo &G, int *K);

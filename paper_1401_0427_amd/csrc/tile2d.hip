@@ -434,26 +434,54 @@ hipError_t launch_tile2d_rest(bool f32, int shape, const void *src, void *dst, c
     return f32 ? tile_any<float>(shape, src, dst, G, M, K, st)
                : tile_any<double>(shape, src, dst, G, M, K, st);
 }
-// Shapes and depths of launches that store every level, by nodes (us per level FP32 /
-// FP64 against single steps, at 96 x 64, 160^2, 256^2, 512^2, 724^2: 1.1 / 1.2 against
-// 3.0, 1.4 / 1.7 against 3.1, 2.3 / 2.9 against 3.3 / 4.1, 5.8 / 7.0 against 6.8 / 12,
-// 11.2 / 18.5 against 12.6 / 22.4).  Beyond the last line the strips that store every
-// level take over on all-periodic grids (724^2: 10.7 / 19.0, 1024^2 FP64 29.7 against
+// Shapes and depths of launches that store every level.  By nodes up to 120 000 (us per level
+// FP32 / FP64 against single steps, at 96 x 64, 160^2, 256^2: 1.1 / 1.2 against 3.0, 1.4 / 1.7
+// against 3.1, 2.3 / 2.9 against 3.3 / 4.1); beyond, the one of two shapes that computes fewer
+// nodes for the grid (512^2 4.4 / 7.1 against 6.6 / 11.8 in 64 x 32, 64 x 4096 5.8 / 8.1 against
+// 6.6 / 11.0 in 32 x 32).  FP64 with faces spills registers in 64 x 32 tiles (512^2 17.6 against
+// 11.3, 700^2 34 against 22): 32 x 32 there (8.1, 15.7).  Beyond the last size the strips that
+// store every level take over on all-periodic grids (724^2 FP32 10.7, 1024^2 FP64 29.7 against
 // 35.4), single steps with faces (1024^2 FP32 20.6 against 21.4).
+//   Flat grids take tiles of 32 x 16 where all are resident, or are not three times as many
+// nodes as the grid, else single steps (20000 x 3 FP64 3.3 against 3.8, but 300000 x 2 57 in 64
+// x 32 tiles, 33 in 32 x 16, 24 in strips, 25.8 in single steps; with faces 170, 37 and 20);
+// narrow ones 16 x 16 (3 x 100000 FP64 15.7 against 81).
 static const struct {
     long nodes;  // at most
     int shape, K;
-} kLevelShapes[] = {
-    {12000, kTile16, 5}, {50000, kTile32x16, 5}, {120000, kTile32x16, 4}, {700000, kTile64x32, 4}};
+} kLevelShapes[] = {{12000, kTile16, 5}, {50000, kTile32x16, 5}, {120000, kTile32x16, 4}};
 
-int tile2d_levels_plan(const Geo &G, int *K)
+// Tiles of a launch (owned nodes wo x ho), and the nodes they compute.
+static double tile_nodes(const Geo &G, int shape, int K, long *tiles)
 {
+    const TileShape &S = kTileShapes[shape];
+    const int wo = S.tx - 2 * K, ho = S.ty * S.R - 2 * K;
+    const long n = (long)((G.nx + wo - 1) / wo) * ((G.ny + ho - 1) / ho);
+    if (tiles) *tiles = n;
+    return (double)n * S.tx * S.ty * S.R;
+}
+
+int tile2d_levels_plan(const Geo &G, bool f32, int *K)
+{
+    const long nodes = (long)G.nx * G.ny;
+    const bool bnd = G.bc[0] != BC_PERIODIC || G.bc[2] != BC_PERIODIC;
+    *K = 4;
+    if (nodes > 5000 && G.ny <= kShortSide) {
+        long n;
+        const double all = tile_nodes(G, kTile32x16, 4, &n);
+        return n <= 256 * kTileShapes[kTile32x16].resident || all <= 3.0 * nodes ? kTile32x16 : -1;
+    }
+    if (nodes > 12000 && G.nx <= kShortSide) return kTile16;
     for (const auto &s : kLevelShapes)
-        if ((long)G.nx * G.ny <= s.nodes) {
+        if (nodes <= s.nodes) {
             *K = s.K;
             return s.shape;
         }
-    return -1;
+    if (nodes > (bnd && !f32 ? 900000 : 700000)) return -1;
+    const double small = tile_nodes(G, kTile32, 4, nullptr);
+    const double large = tile_nodes(G, kTile64x32, 4, nullptr);
+    const bool wide = large < small && !(bnd && !f32);
+    return (wide ? large : small) <= 3.0 * nodes ? (wide ? kTile64x32 : kTile32) : -1;
 }
 
 template <typename T>
@@ -463,6 +491,7 @@ static hipError_t levels_any(int shape, const void *src, void *dst, long stride,
     switch (shape) {
     case kTile16: return tile_launch<T, Phys, true, 16, 16, 1>(src, dst, stride, G, P, K, st);
     case kTile32x16: return tile_launch<T, Phys, true, 32, 16, 1>(src, dst, stride, G, P, K, st);
+    case kTile32: return tile_launch<T, Phys, true, 32, 16, 2>(src, dst, stride, G, P, K, st);
     case kTile64x32: return tile_launch<T, Phys, true, 64, 8, 4>(src, dst, stride, G, P, K, st);
     default: return hipErrorInvalidValue;
     }
