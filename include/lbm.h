@@ -235,8 +235,8 @@ int lbm_moments(lbm_ctx *ctx, const void *state, double *h, double *qx, double *
  *     upstream node x - e_j (across a periodic face: wrapped), across a Neumann
  *     face the node's own plane j, across a wall its own opposite plane with the
  *     momentum normal to the face negated, across an inflow face nowhere;
- *   dLds_partials[b] += sum over the b-th group of nodes (1D: 256 in a row, 2D:
- *     four columns of one row) of lam_np1 . (f^eq(W(v)) - v).
+ *   dLds_partials[b] += sum over the b-th group of nodes (256 in a row; all-periodic 2D
+ *     grids: four columns of one row) of lam_np1 . (f^eq(W(v)) - v).
  * f_n: a caller buffer in the state layout and storage type; lam_np1, lam_n:
  * caller buffers in the state layout whose elements are of the context's
  * adjoint storage (lbm_params.adjoint_storage; lam_n must not alias the

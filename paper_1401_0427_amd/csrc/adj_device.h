@@ -46,7 +46,7 @@ __device__ __forceinline__ double adj_node2d(const double *v, double *l, const P
     return (acc[0] + acc[1]) + acc[2];
 }
 
-// dL/ds of 2D grids is summed per row and group of kAdjGroup columns: one FP64 slot per
+// dL/ds of all-periodic 2D grids is summed per row and group of kAdjGroup columns: one FP64 slot per
 // group, accumulated step by step.  Groups this narrow let every adjoint kernel,
 // whatever its tiling, add exactly the same numbers in the same order, with two
 // cross-lane additions and no LDS.  group_sum: the sum over the lane's aligned group of

@@ -15,8 +15,9 @@
 // where for each component family L0 = sum_j lam_j, L{x,y} = sum_j e_j lam_j
 // (Lxx: x-moment of the gx family, Lyx: y-moment of gx, Lxy: x-moment of gy).
 //
-// Each group of four columns of a row (1D: each workgroup) adds its share of dL/ds to
-// its own FP64 slot (no atomics), so the gradient is deterministic.  The adjoint may be stored in another type than
+// Each workgroup adds its share of dL/ds to its own FP64 slot (no atomics), on all-periodic
+// 2D grids, which run several steps per launch in other tilings (adj_tile.hip), each group of
+// four columns of a row, so the gradient is deterministic.  The adjoint may be stored in another type than
 // the state (TA = double for a float state keeps lambda in double; the
 // arithmetic is double throughout).
 #include "adj_device.h"
@@ -25,7 +26,26 @@
 
 namespace lbm {
 
-template <typename T, typename TA>
+// The sum of the workgroup's shares into its slot.
+__device__ __forceinline__ void block_share(double acc, double *__restrict__ partials)
+{
+    __shared__ double sh[256];
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) partials[blockIdx.x] += sh[0];
+}
+
+// Bound by memory: u^n and lambda^{n+1} read, lambda^n written, 4 bytes a node of partial
+// sums read and written.  A group's sum so far is read with the planes, not behind the
+// arithmetic (1024^2 FP32 29.8 us, 28.5 so), and where the three buffers are beyond the 256
+// MB of the last cache level (NT) lambda^{n+1}, which no other node reads, passes it by and
+// leaves it to the planes that neighbours read again and to the sums: 2048^2 FP32 118 and 97 us,
+// 4096^2 FP32 439 and 427, FP64 897 and 885; 1024^2 FP64, which fits, 46.7 and 52 with it.
+template <typename T, typename TA, bool NT>
 __global__ void __launch_bounds__(256) k_adj2d(const T *__restrict__ un,
                                                const TA *__restrict__ lam1, TA *__restrict__ lam0,
                                                double *__restrict__ partials, Geo G, Phys P,
@@ -35,6 +55,9 @@ __global__ void __launch_bounds__(256) k_adj2d(const T *__restrict__ un,
     const int x = (blockIdx.x - y * tiles_x) * 256 + threadIdx.x;
     const int nx = G.nx, ny = G.ny;
     const long ps = G.ps;
+    const bool lead = x < nx && x % kAdjGroup == 0;
+    double *slot = partials + (lead ? adj_slot(nx, x, y) : 0);
+    const double sum = lead ? *slot : 0.0;
     double acc = 0.0;
     if (x < nx) {
         const long row = (long)y * nx;
@@ -52,7 +75,7 @@ __global__ void __launch_bounds__(256) k_adj2d(const T *__restrict__ un,
             v[4 * k + 3] = ld(b + 3 * ps + rp + x);
         }
 #pragma unroll
-        for (int pl = 0; pl < 12; ++pl) l[pl] = ld(lam1 + pl * ps + row + x);
+        for (int pl = 0; pl < 12; ++pl) l[pl] = ldh<NT ? 1 : 0>(lam1 + pl * ps + row + x);
         acc = adj_node2d<T>(v, l, P);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -64,7 +87,7 @@ __global__ void __launch_bounds__(256) k_adj2d(const T *__restrict__ un,
         }
     }
     acc = group_sum(acc);
-    if (x < nx && x % kAdjGroup == 0) partials[adj_slot(nx, x, y)] += acc;
+    if (lead) *slot = sum + acc;
 }
 
 // ---- faces other than periodic ------------------------------------------------
@@ -144,8 +167,7 @@ __global__ void __launch_bounds__(256) k_adj2d_bnd(const T *__restrict__ un,
             }
         }
     }
-    acc = group_sum(acc);
-    if (x < G.nx && x % kAdjGroup == 0) partials[adj_slot(G.nx, x, y)] += acc;
+    block_share(acc, partials);
 }
 
 // 1D: planes f+ (0), f- (1), g+ (2), g- (3); face 0 = x-, face 1 = x+.  With
@@ -169,7 +191,6 @@ __global__ void __launch_bounds__(256) k_adj1d(const T *__restrict__ un,
                                                double *__restrict__ side, int side_len, Geo G,
                                                Phys P)
 {
-    __shared__ double sh[256];
     const int x = blockIdx.x * 256 + threadIdx.x;
     const int nx = G.nx;
     const long ps = G.ps;
@@ -218,13 +239,7 @@ __global__ void __launch_bounds__(256) k_adj1d(const T *__restrict__ un,
             st(lam0 + 3 * ps + x, 0.0);
         }
     }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partials[blockIdx.x] += sh[0];
+    block_share(acc, partials);
 }
 
 // Adds the Neumann faces' own contributions (side) into lam0: thread i of face
@@ -303,7 +318,8 @@ __global__ void __launch_bounds__(256) k_adj_grad_w0(const T *__restrict__ lam0,
 
 // Each workgroup sums one run of the input (fixed order); a second launch sums
 // the workgroups' results.  One workgroup over the 262 144 groups of a 1024^2 grid took
-// longer than several adjoint steps.
+// longer than several adjoint steps.  (One launch whose last workgroup sums the results: 31 us
+// a call of lbm_sum, 28 so: 256 counts on one address.)
 __global__ void __launch_bounds__(256) k_sum_long(const double *__restrict__ in, long n,
                                                   double *__restrict__ out)
 {
@@ -328,16 +344,20 @@ hipError_t launch_sum_long(const double *in, long n, double *scratch, double *ou
     return e != hipSuccess ? e : launch_sum(scratch, kLongSum, 1, 1, out, st);
 }
 
-long adjoint_blocks(const Geo &G)
-{
-    return G.ny == 1 ? (G.nx + 255) / 256 : adj_slots_row(G.nx) * G.ny;  // 1D : 2D
-}
-
 static bool geo_periodic(const Geo &G)
 {
     return G.bc[0] == BC_PERIODIC && G.bc[1] == BC_PERIODIC && G.bc[2] == BC_PERIODIC &&
            G.bc[3] == BC_PERIODIC;
 }
+
+long adjoint_blocks(const Geo &G)
+{
+    if (G.ny > 1 && geo_periodic(G)) return adj_slots_row(G.nx) * G.ny;
+    return (long)((G.nx + 255) / 256) * G.ny;
+}
+
+// Bytes of u^n, lambda^{n+1} and lambda^n together from which lambda^{n+1} is streamed.
+constexpr double kAdjStream = 4.5e8;
 
 template <typename T, typename TA>
 static void adj_launch(int dim, const void *un, const void *lam1, void *lam0, double *partials,
@@ -347,8 +367,11 @@ static void adj_launch(int dim, const void *un, const void *lam1, void *lam0, do
     if (dim == 1)
         hipLaunchKernelGGL((k_adj1d<T, TA>), dim3(tiles_x), dim3(256), 0, st, (const T *)un,
                            (const TA *)lam1, (TA *)lam0, partials, side, side_len, G, P);
+    else if (geo_periodic(G) && 12.0 * G.ps * (sizeof(T) + 2 * sizeof(TA)) >= kAdjStream)
+        hipLaunchKernelGGL((k_adj2d<T, TA, true>), dim3(tiles_x * G.ny), dim3(256), 0, st,
+                           (const T *)un, (const TA *)lam1, (TA *)lam0, partials, G, P, tiles_x);
     else if (geo_periodic(G))
-        hipLaunchKernelGGL((k_adj2d<T, TA>), dim3(tiles_x * G.ny), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_adj2d<T, TA, false>), dim3(tiles_x * G.ny), dim3(256), 0, st,
                            (const T *)un, (const TA *)lam1, (TA *)lam0, partials, G, P, tiles_x);
     else
         hipLaunchKernelGGL((k_adj2d_bnd<T, TA>), dim3(tiles_x * G.ny), dim3(256), 0, st,
