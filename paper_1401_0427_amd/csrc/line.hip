@@ -162,9 +162,12 @@ __device__ __forceinline__ void line_step(LineNodes<R, PH> &N, const double *in,
 // accesses at a stride of R elements over the banks.
 __device__ __forceinline__ int line_slot(int e) { return e + (e >> 4); }
 
+// The rows of one plane as they lie in memory, and turned into the lane's nodes.  All planes
+// are read before the first is turned, so their loads are in flight together (two steps of
+// 1000 nodes FP32 one plane after the other 4.5 us a launch, MRT 5.2, together 3.9 and 4.4).
 template <typename T, int R>
-__device__ __forceinline__ void line_load(const T *__restrict__ p, T *lds, int lane, int base,
-                                          int nx, bool per, double *v)
+__device__ __forceinline__ void line_read(const T *__restrict__ p, int lane, int base, int nx,
+                                          bool per, T *raw)
 {
     int x = base + lane, s = 64;
     if (per) {
@@ -173,10 +176,16 @@ __device__ __forceinline__ void line_load(const T *__restrict__ p, T *lds, int l
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        lds[line_slot(r * 64 + lane)] = p[per ? x : min(max(x, 0), nx - 1)];
+        raw[r] = p[per ? x : min(max(x, 0), nx - 1)];
         x += s;
         if (per && x >= nx) x -= nx;
     }
+}
+template <typename T, int R>
+__device__ __forceinline__ void line_turn(const T *raw, T *lds, int lane, double *v)
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) lds[line_slot(r * 64 + lane)] = raw[r];
     __asm__ __volatile__("" ::: "memory");
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = (double)lds[line_slot(lane * R + r)];
@@ -226,11 +235,34 @@ __global__ void __launch_bounds__(64 * kLineWaves, 2)
     const bool right = !per && base + 64 * R >= nx, left = !per && !right && base <= 0;
     if (right) base -= (R - (nx - base) % R) % R;
     LineNodes<R, PH> N;
-    if constexpr (kRest<PH>) line_load<T, R>(src, lds, lane, base, nx, per, N.r0);
-#pragma unroll
-    for (int pl = 0; pl < 4; ++pl)
-        line_load<T, R>(src + (NR + pl) * ps, lds, lane, base, nx, per, N.m[pl]);
     const int first = base + lane * R;
+    if constexpr (R == 2) {  // a lane's two nodes, unturned: these launches 3.5 and 3.8 us
+        int x0 = first, x1 = first + 1;
+        if (per) {
+            x0 = ((x0 % nx) + nx) % nx;
+            x1 = x0 == nx - 1 ? 0 : x0 + 1;
+        } else {
+            x0 = min(max(x0, 0), nx - 1);
+            x1 = min(max(x1, 0), nx - 1);
+        }
+        if constexpr (kRest<PH>) {
+            N.r0[0] = ld(src + x0);
+            N.r0[1] = ld(src + x1);
+        }
+#pragma unroll
+        for (int pl = 0; pl < 4; ++pl) {
+            N.m[pl][0] = ld(src + (NR + pl) * ps + x0);
+            N.m[pl][1] = ld(src + (NR + pl) * ps + x1);
+        }
+    } else {
+        T raw[4 + NR][R];
+#pragma unroll
+        for (int pl = 0; pl < 4 + NR; ++pl)
+            line_read<T, R>(src + pl * ps, lane, base, nx, per, raw[pl]);
+        if constexpr (kRest<PH>) line_turn<T, R>(raw[0], lds, lane, N.r0);
+#pragma unroll
+        for (int pl = 0; pl < 4; ++pl) line_turn<T, R>(raw[NR + pl], lds, lane, N.m[pl]);
+    }
     auto steps = [&](auto lc, auto rc) __attribute__((always_inline)) {
         constexpr bool LEFT = decltype(lc)::value, RIGHT = decltype(rc)::value;
         LineFace f0{}, f1{};
@@ -248,10 +280,22 @@ __global__ void __launch_bounds__(64 * kLineWaves, 2)
         steps(std::true_type{}, std::false_type{});
     else
         steps(std::false_type{}, std::false_type{});
-    if constexpr (kRest<PH>) line_store<T, R>(dst, lds, lane, base, ob, oe, N.r0);
+    if constexpr (R == 2) {
 #pragma unroll
-    for (int pl = 0; pl < 4; ++pl)
-        line_store<T, R>(dst + (NR + pl) * ps, lds, lane, base, ob, oe, N.m[pl]);
+        for (int r = 0; r < 2; ++r) {
+            const int x = first + r;
+            if (x >= ob && x < oe) {
+                if constexpr (kRest<PH>) st(dst + x, N.r0[r]);
+#pragma unroll
+                for (int pl = 0; pl < 4; ++pl) st(dst + (NR + pl) * ps + x, N.m[pl][r]);
+            }
+        }
+    } else {
+        if constexpr (kRest<PH>) line_store<T, R>(dst, lds, lane, base, ob, oe, N.r0);
+#pragma unroll
+        for (int pl = 0; pl < 4; ++pl)
+            line_store<T, R>(dst + (NR + pl) * ps, lds, lane, base, ob, oe, N.m[pl]);
+    }
 }
 
 // A whole domain with non-periodic ends of at most 64 R W nodes, K steps.
@@ -379,6 +423,8 @@ static hipError_t line_launch(const void *src, void *dst, const Geo &G, const PH
             whole_launch<T, 2, 1>(src, dst, G, P, K, st);
         else if (G.nx <= 256)
             whole_launch<T, 1, 4>(src, dst, G, P, K, st);
+        else if (G.nx <= 512)  // (16 wavefronts: 400 steps of 257 nodes FP32 220 us, 168 so)
+            whole_launch<T, 1, 8>(src, dst, G, P, K, st);
         else
             whole_launch<T, 1, 16>(src, dst, G, P, K, st);
         return hipGetLastError();
