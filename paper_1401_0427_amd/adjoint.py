@@ -93,14 +93,15 @@ def rollout(h0: torch.Tensor, s: torch.Tensor, T: int, K: int | None = None, lam
             inflow=None) -> torch.Tensor:
     """h(T) from W0 = (h0, 0, 0) (1D: (h0, 0)); differentiable in h0 (a 2D
     (ny, nx) or 1D (nx,) float64 CUDA tensor) and s (0-dim float64 tensor).  K =
-    steps between checkpoints (default about sqrt(T)); K = 1 keeps every level (no
-    recomputation in the backward).  ``bc`` = faces (x-, x+, y-, y+) by name,
+    steps between checkpoints (default sqrt(T) rounded; all-periodic 2D fields, whose
+    sweeps run several steps per launch, the nearest multiple of four from 8 on); K = 1
+    keeps every level (no recomputation in the backward).  ``bc`` = faces (x-, x+, y-, y+) by name,
     ``inflow`` = {face: (h, qx, qy)} as for Solver.  ``adjoint_storage``: element
     type of the adjoint buffers (None = the state's, "f64", or "f32" with FP32
     state storage)."""
     if K is None:
         K = max(1, int(round(math.sqrt(T))))
-        if K > 6:
+        if K > 6 and h0.dim() == 2 and all(b in ("periodic", 0) for b in bc):
             K = (K + 2) // 4 * 4  # segments of whole two-step launches, in even numbers
     return _Rollout.apply(h0, s, int(T), int(K), float(lam), float(g), storage, int(block),
                           adjoint_storage, tuple(bc), inflow)
