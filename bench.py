@@ -27,10 +27,11 @@ Beside it on the same JSON line:
   forms.rest_mrt_*  the paper's rest-population schemes with one relaxation rate per
                  non-conserved moment: D2Q5Q4Q4 on the headline grid (FP64 and FP32
                  storage, several steps per launch, the FP32 L1 error of h; FP64 one
-                 step per launch beside it), D1Q3Q2 on the 1D wall reflection (16
-                 steps per launch; one step beside it) and on the Sec. 2 setup
+                 step per launch beside it), D1Q3Q2 on the 1D wall reflection
+                 (several steps per launch; one step beside it) and on the Sec. 2 setup
   forms.entropy_2d_f64  the discrete entropy diagnostic of the headline state
-  forms.adjoint  2D 1024^2 gradient rollout (T = 500, checkpoints every 23 steps)
+  forms.adjoint  2D 1024^2 gradient rollout (T = 500, checkpoints every 23 steps;
+                 the library's own interval and every level kept beside it)
   roofline       the dominant kernel (the FP64 launches of the timed region's most
                  frequent steps per launch) against its binding roof -- FP64 VALU issue or HBM, named
                  from committed rocprofv3 counters -- with both roofs' figures
@@ -94,60 +95,69 @@ FACES = ("inflow", "neumann", "wall", "inflow")
 FACES_INFLOW = {0: (1.0, 0.2, 0.0), 3: (1.0, 0.0, -0.2)}
 
 
+def _launch_times(torch, S, plan, depth):
+    """Milliseconds of each launch of ``depth`` steps in a run's plan, the launches issued
+    one per lbm_step call; empty where a call of that many steps is not that launch."""
+    top = next(l for l in plan if l["steps"] == depth)
+    if S.run_plan(depth) != [top]:
+        return []
+    st = torch.cuda.current_stream()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(plan) + 1)]
+    ev[0].record(st)
+    for i, l in enumerate(plan):
+        S.step(l["steps"])
+        ev[i + 1].record(st)
+    torch.cuda.synchronize()
+    return [ev[i].elapsed_time(ev[i + 1]) for i, l in enumerate(plan) if l["steps"] == depth]
+
+
 def time_forward(torch, n, storage, steps, warmup, block, npt, pad, fuse=1, keep_h=False,
                  bc=("periodic",) * 4, inflow=None):
     """Forward steps of the headline workload; ``fuse`` = steps per launch asked
-    for (0 = the library's choice; lbm_launch_info reports its plan).  The timed
-    region is one lbm_step call of ``steps`` steps, which regroups a default plan
-    into its fastest launches.  After it (and the final fields) the plan of
-    lbm_launch_plan is issued one launch per call with a HIP event after each, for
-    the average duration of the launches of the dominant kernel (the most frequent
-    steps per launch of the plan).  With ``keep_h`` the final height field is
-    returned under "h"."""
+    for (0 = the library's choice).  The timed region is one lbm_step call of
+    ``steps`` steps, whose launches lbm_run_plan lists.  After it (and the final
+    fields) the same launches are issued one per call with a HIP event after each,
+    for the average duration of those of the dominant kernel (the most frequent
+    steps per launch).  With ``keep_h`` the final height field is returned under
+    "h"."""
     from paper_1401_0427_amd import workloads as W
     from paper_1401_0427_amd.lbm import Solver
 
     c = W.radial_dam_break_2d(n, lam=6.0)
     S = Solver(2, n, n, lam=c.lam, s=c.s, h0=c.h0, qx0=c.qx0, qy0=c.qy0, storage=storage,
                block=block, npt=npt, plane_pad=pad, fuse_steps=fuse, bc=bc, inflow=inflow)
-    info = S.launch_info()
-    K = info["steps_per_launch"]
     S.step(warmup)
     torch.cuda.synchronize()
     st = torch.cuda.current_stream()
-    pieces = S.launch_plan(steps)
+    plan = S.run_plan(steps)
+    pieces = [l["steps"] for l in plan]
     # the dominant kernel: the most frequent launch depth (ties: the deeper one)
     Kd = max(set(pieces), key=lambda k: (pieces.count(k), k))
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(pieces) + 1)]
+    top = next(l for l in plan if l["steps"] == Kd)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     t0 = time.perf_counter()
-    ev[0].record(st)
+    e0.record(st)
     S.step(steps)
-    ev[-1].record(st)
+    e1.record(st)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
-    ms = ev[0].elapsed_time(ev[-1])
+    ms = e0.elapsed_time(e1)
     (h, _, _), tot = S.moments(totals=True)
     ok = bool(torch.isfinite(h).all().item()) and tot[0] > 0
-    ev[0].record(st)
-    for i, k in enumerate(pieces):
-        S.step(k)
-        ev[i + 1].record(st)
-    torch.cuda.synchronize()
-    dur = [ev[i].elapsed_time(ev[i + 1]) for i in range(len(pieces))]
-    full = [d for d, k in zip(dur, pieces) if k == Kd]
+    full = _launch_times(torch, S, plan, Kd) or [ms / len(plan)]
     nodes = n * n
     bpl = 12 * 2 * (8 if storage == "f64" else 4)  # algorithmic bytes per lattice update
     out_h = {"h": h.clone()} if keep_h else {}
     # algorithmic bytes of one launch: the state read once and written once, whatever
     # the number of steps the launch advances
     return dict(ms_per_step=ms / steps, mlups=nodes * steps / (ms * 1e-3) / 1e6,
-                **out_h, steps_per_launch=K, launches=len(pieces),
+                **out_h, steps_per_launch=max(pieces), launches=len(pieces),
                 launch_steps={str(k): pieces.count(k) for k in sorted(set(pieces), reverse=True)},
                 dominant_steps=Kd, periodic=all(b == "periodic" for b in bc),
-                segment_rows=info["segment_rows"], resident_blocks=info["resident_blocks"],
+                kernel=top["kernel"], segment_rows=top["rows"],
                 ms_per_launch=sum(full) / len(full),
                 full_launches=len(full),
-                gbs=nodes * bpl * len(pieces) / (sum(dur) * 1e-3) / 1e9, bytes_per_lu=bpl,
+                gbs=nodes * bpl * len(pieces) / (ms * 1e-3) / 1e9, bytes_per_lu=bpl,
                 bytes_per_launch=nodes * bpl, wall_s=wall, finite=ok, mass=tot[0])
 
 
@@ -174,7 +184,9 @@ def time_1d(torch, storage, steps=2000, warmup=64, fuse=0):
     h = S.moments()[0]
     ok = bool(torch.isfinite(h).all().item())
     bpl = 4 * 2 * (8 if storage == "f64" else 4)
-    return dict(nodes=c.nx, steps=steps, ms_per_step=ms / steps,
+    plan = S.run_plan(steps)
+    return dict(nodes=c.nx, steps=steps, ms_per_step=ms / steps, launches=len(plan),
+                steps_per_launch=max(l["steps"] for l in plan),
                 mlups=c.nx * steps / (ms * 1e-3) / 1e6, effective_gbs=c.nx * bpl * steps / (ms * 1e-3) / 1e9,
                 bytes_per_lu=bpl, finite=ok, h=h.clone())
 
@@ -204,7 +216,7 @@ def time_dam_break_1d(torch, reps=20):
         best = ms if best is None else min(best, ms)
     return dict(nodes=c.nx, steps=c.steps, ms_run=best, ms_per_step=best / c.steps,
                 mlups=c.nx * c.steps / (best * 1e-3) / 1e6,
-                launches=len(S.launch_plan(c.steps)))
+                launches=len(S.run_plan(c.steps)))
 
 
 # Rest weight and moment rates of the timed rest-population runs (one rate per
@@ -227,30 +239,29 @@ def time_rest_2d(torch, n, storage, steps=200, warmup=10, fuse=0):
     c = W.radial_dam_break_2d(n, lam=6.0)
     S = Solver(2, n, n, lam=c.lam, s=c.s, h0=c.h0, qx0=c.qx0, qy0=c.qy0, storage=storage,
                rest=True, a=REST_A, rates=list(REST_RATES_2D), fuse_steps=fuse)
-    K = S.launch_info()["steps_per_launch"]
     S.step(warmup)
     torch.cuda.synchronize()
     st = torch.cuda.current_stream()
-    pieces = S.launch_plan(steps)
+    plan = S.run_plan(steps)
+    pieces = [l["steps"] for l in plan]
     Kd = max(set(pieces), key=lambda k: (pieces.count(k), k))
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(pieces) + 1)]
-    ev[0].record(st)
-    for i, k in enumerate(pieces):
-        S.step(k)
-        ev[i + 1].record(st)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record(st)
+    S.step(steps)
+    e1.record(st)
     torch.cuda.synchronize()
-    ms = ev[0].elapsed_time(ev[-1])
-    full = [ev[i].elapsed_time(ev[i + 1]) for i, k in enumerate(pieces) if k == Kd]
+    ms = e0.elapsed_time(e1)
     (h, _, _), tot = S.moments(totals=True)
     torch.cuda.synchronize()
     hc = h.cpu()
     # the copy's sum against the library's FP64 total of the same moments call
     copy_ok = abs(float(hc.sum()) - tot[0]) <= 1e-9 * abs(tot[0])
+    full = _launch_times(torch, S, plan, Kd) or [ms / len(plan)]
     bpl = 13 * 2 * (8 if storage == "f64" else 4)
     ms_launch = sum(full) / len(full)
     gbs = n * n * bpl / (ms_launch * 1e-3) / 1e9
     return dict(ms_per_step=ms / steps, mlups=n * n * steps / (ms * 1e-3) / 1e6,
-                steps_per_launch=K, dominant_steps=Kd,
+                steps_per_launch=max(pieces), dominant_steps=Kd, launches=len(pieces),
                 launch_steps={str(k): pieces.count(k) for k in sorted(set(pieces), reverse=True)},
                 ms_per_launch=ms_launch, bytes_per_launch=n * n * bpl, gbs=gbs,
                 hbm_frac=gbs / HBM_PEAK_GBS, a=REST_A, rates=list(REST_RATES_2D),
@@ -262,14 +273,15 @@ def time_rest_1d(torch, storage="f64", steps=2000, warmup=64, fuse=0):
     """D1Q3Q2 with moment-space MRT (Sec. 2) on the 1D wall reflection (2^20 nodes):
     5 planes, 80 B (FP64) of state per node update; 40 MiB per buffer, so it runs out
     of the MALL and the rate is an effective bandwidth.  ``fuse`` = steps per launch
-    (0 = library default, 16 here)."""
+    (0 = library default)."""
     from paper_1401_0427_amd import workloads as W
     from paper_1401_0427_amd.lbm import Solver
 
     c = W.wall_reflection_1d()
     S = Solver(1, c.nx, 1, lam=c.lam, s=c.s, bc=c.bc, inflow=c.inflow, h0=c.h0, qx0=c.qx0,
                storage=storage, rest=True, a=0.1, rates=list(REST_RATES_1D), fuse_steps=fuse)
-    K = S.launch_info()["steps_per_launch"]
+    plan = S.run_plan(steps)
+    K = max(l["steps"] for l in plan)
     S.step(warmup)
     torch.cuda.synchronize()
     st = torch.cuda.current_stream()
@@ -281,7 +293,8 @@ def time_rest_1d(torch, storage="f64", steps=2000, warmup=64, fuse=0):
     ms = e0.elapsed_time(e1)
     h = S.moments()[0]
     bpl = 5 * 2 * (8 if storage == "f64" else 4)
-    return dict(nodes=c.nx, steps=steps, steps_per_launch=K, ms_per_step=ms / steps,
+    return dict(nodes=c.nx, steps=steps, steps_per_launch=K, launches=len(plan),
+                ms_per_step=ms / steps,
                 mlups=c.nx * steps / (ms * 1e-3) / 1e6,
                 effective_gbs=c.nx * bpl * steps / (ms * 1e-3) / 1e9, bytes_per_lu=bpl,
                 a=0.1, rates=list(REST_RATES_1D), finite=bool(torch.isfinite(h).all().item()))
@@ -316,7 +329,7 @@ def time_fig1_rest_1d(torch, reps=20):
         ms = e0.elapsed_time(e1)
         best = ms if best is None else min(best, ms)
     return dict(nodes=n, steps=steps, ms_run=best, ms_per_step=best / steps,
-                mlups=n * steps / (best * 1e-3) / 1e6, launches=len(S.launch_plan(steps)))
+                mlups=n * steps / (best * 1e-3) / 1e6, launches=len(S.run_plan(steps)))
 
 
 def time_entropy_2d(torch, n, calls=20):
@@ -461,7 +474,8 @@ def time_adjoint(torch, n=1024, T=500, K=23, storage="f32"):
     """The adjoint workload: 1024^2, T = 500, FP32 forward, checkpoints every K = 23
     steps.  Timed: the forward rollout and the backward sweep (the backward
     recomputes each segment: one library call per segment), with the adjoint stored
-    like the state (the default) and in FP64; beside it the form that keeps every
+    like the state (the default) and in FP64; beside it the library's own interval (24
+    steps) and the form that keeps every
     level (K = 1: the 501 levels take 24 GB, and one library call runs the whole
     backward sweep with no recomputation), when they fit; the gradients against
     those of the FP64 forward (which equals the CPU FP64 oracle's to 1e-15 in the
@@ -492,6 +506,8 @@ def time_adjoint(torch, n=1024, T=500, K=23, storage="f32"):
 
     run(storage, None, K)  # untimed: one-time set-up (module loading, first allocations)
     fwd_s, bwd_s, gh, gs = run(storage, None, K)
+    run(storage, None)
+    fwd_d, bwd_d, gh_d, gs_d = run(storage, None)  # the library's own interval
     _, bwd64, gh64, gs64 = run(storage, "f64", K)
     _, _, gh_ref, gs_ref = run("f64", None, K)
     every = None
@@ -508,6 +524,9 @@ def time_adjoint(torch, n=1024, T=500, K=23, storage="f32"):
     out = dict(n=n, T=T, K=K, storage=storage, adjoint_storage=storage, forward_s=fwd_s,
                backward_s=bwd_s, grad_mlups=n * n * T / (fwd_s + bwd_s) / 1e6,
                every_level=every,
+               default_interval=dict(forward_s=fwd_d, backward_s=bwd_d,
+                                     grad_mlups=n * n * T / (fwd_d + bwd_d) / 1e6,
+                                     same_gradients=bool(torch.equal(gh, gh_d)) and gs == gs_d),
                grad_h0_rel_vs_fp64=rel(gh, gh_ref), grad_s_rel_vs_fp64=abs(gs - gs_ref) / abs(gs_ref),
                backward_s_adjoint_f64=bwd64, grad_h0_rel_vs_fp64_adjoint_f64=rel(gh64, gh_ref),
                grad_s_rel_vs_fp64_adjoint_f64=abs(gs64 - gs_ref) / abs(gs_ref),
@@ -578,11 +597,13 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6  # MI355X: 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x
 
 
 def kernel_kind(form):
-    """Which FP64 step kernel ran the dominant launches of a timed forward form:
-    one step per launch, the LDS two-step kernel (two-step launches on
-    all-periodic grids), else the wave-strip K-step kernel."""
-    if form["dominant_steps"] == 1:
+    """Which FP64 step kernel ran the dominant launches of a timed forward form, as
+    lbm_run_plan names it; without that, one step per launch, the LDS two-step kernel
+    (two-step launches on all-periodic grids), else the wave-strip K-step kernel."""
+    if form["dominant_steps"] == 1 or form.get("kernel") == "step":
         return "one_step"
+    if form.get("kernel") in ("strip", "lds2"):
+        return {"strip": "wave_strip", "lds2": "lds_two_step"}[form["kernel"]]
     if form["dominant_steps"] == 2 and form["periodic"]:
         return "lds_two_step"
     return "wave_strip"
