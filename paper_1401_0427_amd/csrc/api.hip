@@ -608,13 +608,28 @@ static int ensure_chunk(lbm_ctx *c, int from)
 // than 8 + 8 + 4 (4096^2 FP64: 2.18 vs 2.29 ms).  A remainder of one step takes
 // the one-step kernel, the cheapest launch.  even: spread whatever the remainder
 // (regrouped kernels), except that
-//   - FP64 strips of kLoneStepNodes and more keep the one step (us as 7 + 1 and 4 + 4 steps
-//     with faces 4096^2 1338 and 1391, 1500^2 217 and 224, MRT as 5 + 1 and 3 + 3 1390 and
-//     1590; FP32 as 8 + 1 and 5 + 4 2048^2 266 and 198, MRT 4096^2 as 7 + 1 and 4 + 4 1107 and
-//     1022);
+//   - FP64 strips of kLoneStepNodes and more keep the one step where deeper launches cost
+//     more than it: lone_step;
 //   - a run of up to c->alone steps takes one launch (1024^2 FP64 8 steps 95, 4 + 4 104);
 //   - two steps where c->apart run as single ones.
 static const long kLoneStepNodes = 2000000;
+// Whether a remainder of one step stays one launch (us as m F + 1 steps and spread over the
+// m + 1 launches).  Periodic 9-step launches cost more than 8-step ones (4096^2 790 and 740),
+// so only 9 + 1 does, on grids of 2 kLoneStepNodes: 4096^2 10 steps 1314 and 1398, 2048^2 376
+// and 382, but 1500^2 252 and 232, and 4096^2 19 steps 2118 and 2097, 100 steps 9339 and
+// 8987.  With faces and MRT the depths differ less: 4096^2 with faces 8 steps 1333 and 1421,
+// 22 2802 and 2833, 36 4326 and 4295, 1500^2 8 steps 219 and 250, 78 1528 and 1546; MRT 4096^2
+// 7 steps 1459 and 1569, 19 3090 and 3104, 67 9922 and 9753, 2048^2 7 steps 376 and 387, 67
+// 2520 and 2524: always below 3 kLoneStepNodes, else up to three launches.  FP32 always
+// spreads (8 + 1 and 5 + 4 2048^2 266 and 198, MRT 4096^2 7 + 1 and 4 + 4 1107 and 1022).
+static bool lone_step(const lbm_ctx *c, long F, long todo)
+{
+    const long nodes = (long)c->G.nx * c->G.ny;
+    if (todo % F != 1 || c->tile != kRunStrips || c->f32 || nodes < kLoneStepNodes) return false;
+    const bool bnd = c->G.bc[0] != BC_PERIODIC || c->G.bc[2] != BC_PERIODIC;
+    if (!bnd && !c->rest) return todo == F + 1 && nodes >= 2 * kLoneStepNodes;
+    return nodes < 3 * kLoneStepNodes || todo <= 3 * F + 1;
+}
 static int next_launch_steps(const lbm_ctx *c, long F, bool even, long todo)
 {
     if (todo <= 1 || F <= 1) return (int)(todo < 1 ? todo : 1);
@@ -622,9 +637,7 @@ static int next_launch_steps(const lbm_ctx *c, long F, bool even, long todo)
     if (even) {
         if (todo <= c->alone) return (int)todo;
         if (todo == 2 && c->apart) return 1;
-        if (r == 1 && c->tile == kRunStrips && !c->f32 &&
-            (long)c->G.nx * c->G.ny >= kLoneStepNodes)
-            return (int)(todo < F ? todo : F);
+        if (lone_step(c, F, todo)) return (int)(todo < F ? todo : F);
     }
     if (!even && (c->dim != 2 || r <= 1)) return (int)(todo < F ? todo : F);
     const long launches = (todo + F - 1) / F;

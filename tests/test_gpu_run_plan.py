@@ -89,3 +89,25 @@ def test_rejected():
     R = gpu_solver(smooth_random_2d(20, 20), rest=True, a=0.05)
     assert L.lbm_run_plan(R.ctx, 2, 5, None, 0, None) == lbm.LBM_EINVAL
     assert L.lbm_run_plan(None, 0, 5, None, 0, None) == lbm.LBM_ESTATE
+
+
+@pytest.mark.parametrize("n,rest,faces,steps,lone", [
+    (2048, False, False, 10, True), (2048, False, False, 19, False), (2048, False, False, 100, False),
+    (1500, False, False, 10, False), (2048, False, True, 50, True), (3000, False, True, 22, True),
+    (3000, False, True, 78, False), (2048, True, False, 67, True), (3000, True, False, 67, False)])
+def test_one_step_left_over(n, rest, faces, steps, lone):
+    """A remainder of one step is a launch of its own only where the deeper launches that
+    it leaves cost less than spreading it."""
+    import torch
+
+    from paper_1401_0427_amd.lbm import Solver
+
+    kw = dict(rest=True, a=0.05, rates=[1.7] * 10) if rest else {}
+    S = Solver(2, n, n, lam=6.0, s=1.7, h0=torch.ones(n, n, dtype=torch.float64).numpy(),
+               **(FACES if faces else {}), **kw)
+    depths = [l["steps"] for l in S.run_plan(steps)]
+    most = max(depths)
+    assert sum(depths) == steps and len(depths) == -(-steps // max(most, 6))
+    assert (depths[-1] == 1 and set(depths[:-1]) == {most}) == lone
+    if not lone:
+        assert most - min(depths) <= 1
