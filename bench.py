@@ -585,6 +585,9 @@ KERNELS = {
                    "k_step2d_xk_fwd_4096_sq.json",
                    "k_step2d_xk<double, {K}> ({K} pull-stream + BGK collide steps per launch, "
                    "one wavefront per column strip)"),
+    "tile": (("tile2d.hip", "lbm_device.h"), "k_tile2d_fwd_300_traffic.json",
+             "k_tile2d_fwd_300_sq.json",
+             "k_tile2d<double> ({K} pull-stream + BGK collide steps per launch, tiles in registers)"),
 }
 
 # FP64 operations of one node update as the scheme states them (Sec. 1-3 at a = 0,
@@ -602,8 +605,8 @@ def kernel_kind(form):
     (two-step launches on all-periodic grids), else the wave-strip K-step kernel."""
     if form["dominant_steps"] == 1 or form.get("kernel") == "step":
         return "one_step"
-    if form.get("kernel") in ("strip", "lds2"):
-        return {"strip": "wave_strip", "lds2": "lds_two_step"}[form["kernel"]]
+    if form.get("kernel") in ("strip", "lds2", "tile"):
+        return {"strip": "wave_strip", "lds2": "lds_two_step", "tile": "tile"}[form["kernel"]]
     if form["dominant_steps"] == 2 and form["periodic"]:
         return "lds_two_step"
     return "wave_strip"

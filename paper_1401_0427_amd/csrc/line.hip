@@ -8,9 +8,9 @@
 // and no barrier in the step loop, so the FP64 issue rate bounds it (at 2^20 nodes;
 // on small domains the chain of about 25 dependent FP64 operations of one step).
 // Against one node per thread of a 1024-thread workgroup with the planes in LDS and a
-// barrier per step: 2^20 nodes FP64 1.9 us a step (2.5 before), 2^18 0.68 (1.0), 2000
-// to 30000 0.31 - 0.35 (0.5 - 0.55), 1000 with ends 0.31 (0.51), 80 with a rest
-// population 0.33 (0.73).
+// barrier per step, us a step FP64: 2^20 nodes 1.63 (2.5 before), 2^18 0.61 (1.0), 2000 to
+// 30000 0.23 - 0.25 (0.5 - 0.55), 1000 with ends 0.25 (0.51), 80 with a rest population 0.37
+// (0.73); one step per launch 15.9, 3.7, 2.3 - 2.5, 2.2, 1.9.
 //   k_line: the domain is cut into tiles of `nout` output nodes, one wavefront each,
 //     with K nodes of halo per side inside the domain (each step invalidates one more
 //     node at either end).  Tiles start at multiples of R, so the domain's first node

@@ -321,22 +321,27 @@ static int short_plan(const Geo &G, bool rest, bool f32, bool bnd, bool strips, 
     return kTile32x16;
 }
 
-// Shape by the number of nodes (measured fastest, us per step FP64 a = 0 with inflow /
-// wall / Neumann faces against one step per launch, at 35 x 20, 70 x 40, 140 x 80,
-// 280 x 160, 560 x 320: 0.94 / 4.75, 1.03 / 4.2, 1.34 / 4.3, 2.1 / 5.6, 3.9 / 8.9; all
-// periodic 0.80 / 2.7, 0.93 / 2.9, 1.2 / 3.1, 1.9 / 4.4, 3.4 / 8.9).  What changes at a
-// limit is how many tiles fall on the fullest compute unit: 400 x 300 with faces in tiles
-// of 64 x 24 FP64 2.7, FP32 2.5, of 64 x 32 (at a smaller depth) 3.3, 3.0; 160 x 140 in
-// 32 x 16 1.5, in 32 x 32 1.9; 640 x 600 in 32 x 32 tall 6.1, in 64 x 32 7.1.  On larger grids
-// the wave-strip launches take over (us a step tile / strips on square grids: periodic
-// FP64 250 000 nodes 4.2 / 4.6, 302 000 5.3 / 4.6, 577 000 8.4 / 5.6; FP32 360 000 4.4 /
-// 4.7, 462 000 5.2 / 4.8, 883 000 8.2 / 6.9; with faces FP64 462 000 7.7 / 8.5, 722 000
-// 11.0 / 10.8, FP32 1.05 M 11.0 / 11.9, 1.7 M 15.6 / 12.7; MRT periodic FP64 202 000 4.4 /
-// 4.8, 302 000 6.2 / 4.9, 722 000 12.0 / 7.1, FP32 360 000 6.2 / 6.4, 577 000 9.0 / 7.1).
-// MRT with faces has no strip launch: tiles throughout (4.2 M nodes FP64 71 us against
-// 163 for one step per launch).  The limits count the nodes of whole output tiles, and
-// grow with the columns that whole strips cover beyond the grid's (200 x 2000 FP64: 5.9 /
-// 6.5; 2000 x 200: 6.0 / 5.1).  strip_cols: those columns, 0 where no strip launch runs.
+// Shape by the number of nodes; the limits are from grids of 7 : 4 (measured fastest, us per
+// step FP64 a = 0 with inflow / wall / Neumann faces against one step per launch, at 35 x 20,
+// 70 x 40, 140 x 80, 280 x 160, 560 x 320: 0.94 / 4.75, 1.03 / 4.2, 1.34 / 4.3, 2.1 / 5.6,
+// 3.9 / 8.9; all periodic 0.80 / 2.7, 0.93 / 2.9, 1.2 / 3.1, 1.9 / 4.4, 3.4 / 8.9).  What
+// decides is how many tiles fall on the fullest compute unit, which on such grids goes by the
+// nodes: 400 x 300 with faces in tiles of 64 x 24 FP64 2.7, FP32 2.5, of 64 x 32 (at a smaller
+// depth) 3.3, 3.0; 160 x 140 in 32 x 16 1.5, in 32 x 32 1.9; 640 x 600 in 32 x 32 tall 6.1, in
+// 64 x 32 7.1.  A long grid of as many nodes makes more tiles and would change shape at other
+// sizes (FP64 periodic, this shape / the fastest of the six at any depth / single steps:
+// 1500 x 16 1.60 / 1.60 / 3.8, 1200 x 24 1.75 / 1.75 / 3.5, 40 x 2500 2.59 / 2.30 / 6.2,
+// 1000 x 100 2.49 / 2.35 / 5.4, 4000 x 60 3.75 / 3.74 / 11.0, 60 x 4000 5.9 / 4.2 / 11.9; of
+// 96 such runs in all kinds half are within 5 %, all but 7 within 20 %, the worst 51 %).
+//   On larger grids the wave-strip launches take over (us a step tile / strips on square
+// grids: periodic FP64 250 000 nodes 4.2 / 4.6, 302 000 5.3 / 4.6, 577 000 8.4 / 5.6; FP32
+// 360 000 4.4 / 4.7, 462 000 5.2 / 4.8, 883 000 8.2 / 6.9; with faces FP64 462 000 7.7 / 8.5,
+// 722 000 11.0 / 10.8, FP32 1.05 M 11.0 / 11.9, 1.7 M 15.6 / 12.7; MRT periodic FP64 202 000
+// 4.4 / 4.8, 302 000 6.2 / 4.9, 722 000 12.0 / 7.1, FP32 360 000 6.2 / 6.4, 577 000 9.0 /
+// 7.1).  MRT with faces has no strip launch: tiles throughout (4.2 M nodes FP64 71 us against
+// 163 for one step per launch).  These limits count the nodes of whole output tiles, and grow
+// with the columns that whole strips cover beyond the grid's (200 x 2000 FP64: 5.9 / 6.5;
+// 2000 x 200: 6.0 / 5.1).  strip_cols: those columns, 0 where no strip launch runs.
 int tile2d_plan(const Geo &G, bool rest, bool f32, long strip_cols, int *K)
 {
     const bool bnd = G.bc[0] != BC_PERIODIC || G.bc[2] != BC_PERIODIC;

@@ -23,7 +23,7 @@ def test_forward_form(n, steps, fuse):
     assert out["launch_steps"] == {str(k): pieces.count(k) for k in sorted(set(pieces), reverse=True)}
     top = next(l for l in plan if l["steps"] == out["dominant_steps"])
     assert (out["kernel"], out["segment_rows"]) == (top["kernel"], top["rows"])
-    kind = {"step": "one_step", "lds2": "lds_two_step"}.get(top["kernel"], "wave_strip")
+    kind = {"step": "one_step", "lds2": "lds_two_step", "strip": "wave_strip", "tile": "tile"}[top["kernel"]]
     assert bench.kernel_kind(out) == kind
 
 
